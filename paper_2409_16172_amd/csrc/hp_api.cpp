@@ -589,15 +589,16 @@ hp_status hp_plan_create(hp_plan* out, const hp_grid* grid, double omega, const 
       if ((m >> k) & 1ull) { need[(size_t)k * n0 + i0] = 1; P->slabs_used += 1.0; }
   }
   // store masks of the symbol pass: bit e of thread j = axis-0 index j + Tb*e (for
-  // mixed-radix lengths, with the built-in plan's Tb; a tuned plan with another
-  // thread count reads `need` directly)
+  // mixed-radix lengths, with the built-in kernel's Tb; one with another thread
+  // count reads `need` directly)
   std::vector<uint16_t> smask(1, 0);
   P->smask_thr = 0;
   {
     const bool gen = hp::cols_use_gen(P->real_kind(), n0);
-    const int Tb = gen ? hp::gen_symbol_line_threads(P->real_kind(), n0)
+    int Eb = 0;
+    const int Tb = gen ? hp::gen_symbol_line_threads(P->real_kind(), n0, &Eb)
                        : hp::symbol_pass_line_threads(P->real_kind(), n0);
-    const int Eb = gen ? hp::gen_symbol_elems(P->real_kind()) : n0 / Tb;
+    if (!gen) Eb = n0 / Tb;
     if (Tb > 0 && Eb <= 16) {
       if (gen) P->smask_thr = Tb;
       smask.assign((size_t)P->K * Tb, 0);
@@ -1734,11 +1735,11 @@ hp_status hp_plan_autotune(hp_plan p, double* before_ms, double* after_ms, void*
   const size_t S0 = p->npts / p->n[0];
   // per slot: candidate kind, line length, lines across, mode
   struct Slot { int kind, n, S, mode; bool used; };
-  const Slot slots[5] = {{hp::kTuneRows, nl, 1, 0, true},
+  const Slot slots[5] = {{hp::kTuneRows, nl, (int)(p->npts / nl), 0, true},
                          {hp::kTuneCols, p->n[1], p->n[2], 0, p->dim == 3},
                          {hp::kTuneCols, p->n[0], (int)S0, 1, true},
                          {hp::kTuneCols, p->n[1], p->n[2], 0, p->dim == 3},
-                         {hp::kTuneCombine, nl, 1, 0, true}};
+                         {hp::kTuneCombine, nl, (int)(p->npts / nl), 0, true}};
   // the fastest of three timings of every pass (the in-place 3-D passes run once per apply)
   auto measure = [&](double* t) -> hipError_t {
     for (int i = 0; i < 5; ++i) t[i] = INFINITY;

@@ -103,6 +103,42 @@ inline bool is_pow2_len(int n) { return n > 0 && (n & (n - 1)) == 0; }
 // 2048, whose register-tile column kernel would not fit in LDS.
 bool cols_use_gen(int real_kind, int n);
 
+// Mixed-radix lines held in registers (hp_lines.hip): T = n / (smallest radix) threads
+// per line, one butterfly per thread and stage, L lines per workgroup.
+constexpr int kLineStages = 4;
+constexpr int kLineMaxThr = 512;   // threads per workgroup (two waves per SIMD: up to 256 VGPRs)
+enum LineKind { kLineRows = 0, kLineCols = 1, kLineSym = 2, kLineComb = 3 };
+// Largest stage radix, and the one of the passes B and C that hold a line's spectrum or
+// sums across transforms when a length needs no more stages that way: their kernels then
+// fit three FP64 or four FP32 waves per SIMD instead of two or three.
+constexpr int kLineRadixMax = 16, kLineRadixLo = 10;
+// Elements of a line that passes B and C hold across transforms (the spectrum with its
+// lambda; the sums with the points' records) beside the butterfly in flight: the last
+// forward radix of a plan, its smallest, is at most this.
+template <typename R, int RM>
+constexpr int line_spectrum_max() { return sizeof(R) == 8 && RM > 12 ? 12 : RM; }
+constexpr int kLineSplits = 4;   // node splits of pass C at most
+struct LinePlan {
+  int n, nst, T, L;
+  int rm;                      // the radix bound of the kernel (kLineRadixLo or kLineRadixMax)
+  int splits;                  // pass C: the L lines are L / splits rows, each split over its nodes
+  int two_buf;                 // 1: exchanges alternate between two LDS regions
+  int r[kLineStages];          // radices in stage order
+  int K[kLineStages];          // product of the earlier radices
+  int J[kLineStages];          // product of the later ones
+  int pitch[kLineStages - 1];  // LDS row pitch of the exchange after each stage
+  int slots, twn;              // LDS elements of a line and of the stage tables
+};
+// The plan of one pass over lines of length n: `across` of them side by side (rows, or
+// the columns of a slab), `groups` such sets (slabs and fields; node fields of pass B; of
+// pass C the nodes); lines_req > 0 asks for that many lines (rows) per workgroup (ignored
+// when they do not fit).  False: a length these kernels do not take (powers of two;
+// lengths without at most four radices and kLineMaxThr threads).
+bool make_line_plan(int real_kind, int n, int kind, int across, int groups, int lines_req, LinePlan* out);
+// Threads per line whose store masks pass B reads (bit t of thread j: axis-0 index
+// j + threads * t) and the elements each stores; 0 if these kernels do not take n.
+int line_symbol_threads(int real_kind, int n, int* elems);
+
 // Run-time choices of a transform pass (0 = the built-in choice): threads per line,
 // lines per workgroup (column passes) and radix schedule of the mixed-radix passes,
 // node groups per column tile of the power-of-two symbol pass, node splits (1 or 4)
@@ -153,6 +189,10 @@ struct ColsArgs {
   const hipEvent_t* tev = nullptr;   // timing events of the launch (see launch_rows_fwd)
 };
 hipError_t launch_cols(const ColsArgs& a, hipStream_t st);
+hipError_t launch_line_rows(int real_kind, int in_kind, const LinePlan& p, const void* in, void* out, int rows,
+                            size_t in_rs, size_t out_rs, int nrhs, const void* tw, const int* skip, hipStream_t st,
+                            const hipEvent_t* tev);
+hipError_t launch_line_cols(const LinePlan& p, const ColsArgs& a, hipStream_t st);
 
 // Pass C: inverse transform along the contiguous axis of the K node fields and
 // the interpolation combine.  out_kind: 0 = complex128, 1 = complex64.
@@ -178,12 +218,12 @@ struct CombineArgs {
 };
 constexpr int kLagTable = kMaxNodes * 5;
 hipError_t launch_combine(const CombineArgs& a, hipStream_t st);
+hipError_t launch_line_combine(const LinePlan& p, const CombineArgs& a, hipStream_t st);
 int combine_group_rows(int real_kind, int n);        // rows per workgroup of pass C
 int symbol_pass_line_threads(int real_kind, int n);  // threads per line T of pass B
 // threads per line of the built-in mixed-radix symbol-pass plan (0 if n has none) and
 // the elements each thread holds
-int gen_symbol_line_threads(int real_kind, int n);
-int gen_symbol_elems(int real_kind);
+int gen_symbol_line_threads(int real_kind, int n, int* elems);
 
 // Stencil.  kind: 0 = FP64 (c128 -> c128), 1 = FP32 arithmetic c64 -> c64,
 // 2 = FP32 arithmetic c64 -> c128, 3 = FP64 residual y = f - P u (c128).

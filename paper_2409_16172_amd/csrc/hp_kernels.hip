@@ -15,27 +15,9 @@
 #include <mutex>
 #include <type_traits>
 
-#include <hip/hip_ext.h>
-
-#include "hp_internal.h"
-
-// Launch of a pass kernel; with timing events (tev non-null) through
-// hipExtLaunchKernelGGL, which stores the kernel's own start and end times in
-// tev[0] and tev[1] (no marker packets around it).
-#define HP_PASS_LAUNCH(tev, kernel, grid, block, shm, st, ...)                                         \
-  do {                                                                                                 \
-    if ((tev) != nullptr)                                                                              \
-      hipExtLaunchKernelGGL(kernel, grid, block, (std::uint32_t)(shm), st, (tev)[0], (tev)[1], 0, __VA_ARGS__); \
-    else                                                                                               \
-      hipLaunchKernelGGL(kernel, grid, block, shm, st, __VA_ARGS__);                                    \
-  } while (0)
+#include "hp_device.h"
 
 namespace hp {
-
-template <typename R, typename S>
-__device__ __forceinline__ cpx<R> cvt(cpx<S> a) {
-  return {(R)a.re, (R)a.im};
-}
 
 // Rows (contiguous axis): G lines of length N per workgroup of 256 threads
 // (one line per workgroup when a line needs 256 threads or more).
@@ -179,21 +161,6 @@ __global__ __launch_bounds__((RowCfg<R, N>::THREADS)) void k_rows_fwd(const cpx<
 }
 
 // ---------------------------------------------------------------- strided passes
-// 1/x for finite x > 0: hardware reciprocal estimate refined by Newton-Raphson
-// steps r <- r + r (1 - x r) (two in FP64, one in FP32).
-__device__ __forceinline__ double recip(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  double e = __builtin_fma(-x, r, 1.0);
-  r = __builtin_fma(r, e, r);
-  e = __builtin_fma(-x, r, 1.0);
-  return __builtin_fma(r, e, r);
-}
-__device__ __forceinline__ float recip(float x) {
-  float r = __builtin_amdgcn_rcpf(x);
-  const float e = __builtin_fmaf(-x, r, 1.0f);
-  return __builtin_fmaf(r, e, r);
-}
-
 // Symbol multiply of one node on the elements a thread holds.  The denominator
 // A_n - g_n lambda is formed in FP64 (it cancels near |xi| = omega/|gamma_n|),
 // then reciprocated in the working precision.
@@ -328,86 +295,6 @@ __global__ __launch_bounds__((ColsCfg<R, N, MODE>::THREADS)) void k_cols(
 }
 
 // ---------------------------------------------------------------- pass C
-// Interpolation record of one point: pos >= 0 encodes the real-axis segment
-// seg + t (weights 1-t on node seg, t on node seg+1); pos < 0 encodes the layer
-// segment, -(1 + j + t): weights 1-t on the lower layer node (c_o itself for
-// j = 0) and t on layer node j+1 (Eqn. 405 with Re gamma = c_o in the layer).
-__device__ __forceinline__ void decode_pos(double p, int M, int Mt, int mo, int& A, int& B, double& t) {
-  if (p >= 0.0) {
-    if (M == 1) {
-      A = 0; B = 0; t = 0.0;
-      return;
-    }
-    int s = (int)p;
-    if (s > M - 2) s = M - 2;
-    A = s; B = s + 1; t = p - (double)s;
-  } else {
-    const double q = -p - 1.0;
-    int s = (int)q;
-    if (s > Mt - 1) s = Mt - 1;
-    A = (s == 0) ? mo : M + s - 1; B = M + s; t = q - (double)s;
-  }
-}
-
-// Interpolation modes of the combine: piecewise linear along Re gamma (the
-// paper's), piecewise Lagrange of degree >= 2 along the real axis, and bilinear in
-// (c, a) (one damping node axis; no layer).
-enum InterpMode { kInterpLinear = 0, kInterpLagrange = 1, kInterpBilinear = 2 };
-
-// Per-point record for the combine: `ab` packs nodes A, B (piecewise linear:
-// weights 1-t, t) or, for a real-axis point under Lagrange interpolation of degree
-// ord >= 2, the first node A of its ord+1-node stencil and a flag; `tt` holds t,
-// or the point's speed x for the Lagrange weights.  Bilinear: `ab` packs the four
-// nodes (s, r), (s+1, r), (s, r+1), (s+1, r+1) of node index m + M r, `tt` and `uu`
-// the fractions along c and along a.  lag: the table of CombineArgs.
-template <typename R, int IM>
-__device__ __forceinline__ void interp_record(double pv, double pa, int M, int Mt, int mo, int Ma, int ord,
-                                              const double* lag, int& ab, R& tt, R& uu) {
-  int A = -1, B = -1;
-  double t = 0.0;
-  decode_pos(pv, M, Mt, mo, A, B, t);
-  if (IM == kInterpBilinear) {
-    int r = (int)pa;
-    if (r > Ma - 2) r = Ma - 2;
-    if (r < 0) r = 0;
-    const double u = pa - (double)r;
-    A += M * r;
-    B += M * r;
-    ab = A | (B << 8) | ((A + M) << 16) | ((B + M) << 24);
-    tt = (R)t;
-    uu = (R)u;
-  } else if (IM == kInterpLagrange && pv >= 0.0 && M > 1) {
-    int a = A - (ord - 1) / 2;
-    a = a < 0 ? 0 : (a > M - 1 - ord ? M - 1 - ord : a);
-    ab = a | (1 << 16);
-    tt = (R)(lag[A] + t * (lag[A + 1] - lag[A]));
-  } else {
-    ab = (A & 0xff) | ((B & 0xff) << 8);
-    tt = (R)t;
-  }
-}
-
-// Weight of node n at a point with record (ab, tt, uu).
-template <typename R, int IM>
-__device__ __forceinline__ R interp_weight(int ab, R tt, R uu, int n, int ord, const double* lag) {
-  const int A = ab & 0xff;
-  if (IM == kInterpBilinear) {
-    const int B = (ab >> 8) & 0xff, Cn = (ab >> 16) & 0xff, D = (ab >> 24) & 0xff;
-    const R lo = (R)1 - uu;
-    return (A == n ? ((R)1 - tt) * lo : (R)0) + (B == n ? tt * lo : (R)0) + (Cn == n ? ((R)1 - tt) * uu : (R)0) +
-           (D == n ? tt * uu : (R)0);
-  }
-  if (IM == kInterpLagrange && (ab >> 16)) {
-    if (n < A || n > A + ord) return (R)0;
-    R w = (R)lag[kMaxNodes + 4 * n + (n - A)];
-    for (int k = A; k <= A + ord; ++k)
-      if (k != n) w *= tt - (R)lag[k];
-    return w;
-  }
-  const int B = (ab >> 8) & 0xff;
-  return (A == n ? (R)1 - tt : (R)0) + (B == n ? tt : (R)0);
-}
-
 // NS > 1 (lines of at most one wavefront, few rows): NS wavefronts share the
 // workgroup's rows, wavefront s taking every NS-th node the rows use, and their
 // partial sums meet in LDS at the end; the node loop is NS times shorter and the
@@ -669,150 +556,6 @@ __global__ __launch_bounds__(64 * kWaveRows, 2) void k_comb_wave(
 __host__ __device__ __forceinline__ int gpos(int p) { return HP_GEN_PAD ? p + (p >> 4) : p; }
 // LDS slots a line of n elements takes
 __host__ __device__ __forceinline__ size_t gen_line_slots(int n) { return (size_t)gpos(n - 1) + 1; }
-
-// cos and sin of 2 pi m / r, evaluated at compile time for the butterflies' fixed
-// roots: the angle is reduced to [0, pi/4] by the octant symmetries (exactly, in
-// integers), then summed as a Taylor series.
-constexpr double kPiD = 3.14159265358979323846;
-constexpr double taylor_sin(double x) {
-  double t = x, s = x;
-  for (int k = 1; k < 14; ++k) { t *= -x * x / ((2.0 * k) * (2.0 * k + 1.0)); s += t; }
-  return s;
-}
-constexpr double taylor_cos(double x) {
-  double t = 1.0, s = 1.0;
-  for (int k = 1; k < 14; ++k) { t *= -x * x / ((2.0 * k - 1.0) * (2.0 * k)); s += t; }
-  return s;
-}
-// angle 2 pi m / r with 0 <= m <= r/8 (at most pi/4)
-constexpr void small_cs(long m, long r, double& c, double& s) {
-  const double x = 2.0 * kPiD * (double)m / (double)r;
-  c = taylor_cos(x);
-  s = taylor_sin(x);
-}
-constexpr void root_cs(long m, long r, double& c, double& s) {
-  m %= r;
-  double sg = 1.0;
-  if (2 * m > r) { m = r - m; sg = -1.0; }           // sin(2 pi - x) = -sin x
-  double cg = 1.0;                                   // now x in [0, pi]
-  if (4 * m > r) { m = r - 2 * m; cg = -1.0; r *= 2; }  // x -> pi - x: cos flips; m/r -> (r/2 - m)/r
-  // now x = 2 pi m / r in [0, pi/2]
-  double cc = 0.0, ss = 0.0;
-  if (8 * m > r) {                                   // x -> pi/2 - x swaps cos and sin
-    small_cs(r - 4 * m, 4 * r, ss, cc);
-  } else {
-    small_cs(m, r, cc, ss);
-  }
-  c = cg * cc;
-  s = sg * ss;
-}
-template <int RAD>
-struct RootTab {
-  double c[RAD], s[RAD];
-};
-template <int RAD>
-constexpr RootTab<RAD> make_roots() {
-  RootTab<RAD> t{};
-  for (int m = 0; m < RAD; ++m) root_cs(m, RAD, t.c[m], t.s[m]);
-  return t;
-}
-template <int RAD>
-constexpr RootTab<RAD> kRoots = make_roots<RAD>();
-
-// x exp(DIR 2 pi i m / RAD) for a fixed m (the quarter turns without multiplies)
-template <typename R, int RAD, int DIR>
-__device__ __forceinline__ cpx<R> mul_root(cpx<R> x, int m) {
-  m %= RAD;
-  if (m == 0) return x;
-  if (2 * m == RAD) return {-x.re, -x.im};
-  if (4 * m == RAD) return DIR > 0 ? cpx<R>{-x.im, x.re} : cpx<R>{x.im, -x.re};
-  if (4 * m == 3 * RAD) return DIR > 0 ? cpx<R>{x.im, -x.re} : cpx<R>{-x.im, x.re};
-  const R c = (R)kRoots<RAD>.c[m], sn = (R)(DIR * kRoots<RAD>.s[m]);
-  return {x.re * c - x.im * sn, x.re * sn + x.im * c};
-}
-
-// DFTs of length 2, 3, 4 and 5 in place: out[k] = sum_t v[t] exp(DIR 2 pi i t k / RAD),
-// with the symmetric pairs of terms combined.
-template <typename R, int DIR>
-__device__ __forceinline__ void dft2(cpx<R>& a, cpx<R>& b) {
-  const cpx<R> s = cadd(a, b), d = csub(a, b);
-  a = s;
-  b = d;
-}
-template <typename R, int DIR>
-__device__ __forceinline__ cpx<R> times_dir_i(cpx<R> x) {   // DIR i x
-  return DIR > 0 ? cpx<R>{-x.im, x.re} : cpx<R>{x.im, -x.re};
-}
-template <typename R, int RAD, int DIR>
-__device__ __forceinline__ void dft_prime(cpx<R> (&v)[RAD]) {
-  if constexpr (RAD == 2) {
-    dft2<R, DIR>(v[0], v[1]);
-  } else if constexpr (RAD == 3) {
-    constexpr double s3 = 0.86602540378443864676;   // sin(2 pi / 3)
-    const cpx<R> a = cadd(v[1], v[2]);
-    const cpx<R> d = csub(v[1], v[2]);
-    const cpx<R> m = {v[0].re - (R)0.5 * a.re, v[0].im - (R)0.5 * a.im};
-    const cpx<R> j = times_dir_i<R, DIR>(cpx<R>{(R)s3 * d.re, (R)s3 * d.im});
-    v[0] = cadd(v[0], a);
-    v[1] = cadd(m, j);
-    v[2] = csub(m, j);
-  } else if constexpr (RAD == 4) {
-    const cpx<R> s02 = cadd(v[0], v[2]), d02 = csub(v[0], v[2]);
-    const cpx<R> s13 = cadd(v[1], v[3]), d13 = times_dir_i<R, DIR>(csub(v[1], v[3]));
-    v[0] = cadd(s02, s13);
-    v[2] = csub(s02, s13);
-    v[1] = cadd(d02, d13);
-    v[3] = csub(d02, d13);
-  } else {
-    static_assert(RAD == 5, "radix 2, 3, 4 or 5");
-    constexpr double c1 = 0.30901699437494742410, s1 = 0.95105651629515357212;   // 2 pi / 5
-    constexpr double c2 = -0.80901699437494742410, s2 = 0.58778525229247312917;  // 4 pi / 5
-    const cpx<R> a1 = cadd(v[1], v[4]), b1 = csub(v[1], v[4]);
-    const cpx<R> a2 = cadd(v[2], v[3]), b2 = csub(v[2], v[3]);
-    const cpx<R> m1 = {v[0].re + (R)c1 * a1.re + (R)c2 * a2.re, v[0].im + (R)c1 * a1.im + (R)c2 * a2.im};
-    const cpx<R> m2 = {v[0].re + (R)c2 * a1.re + (R)c1 * a2.re, v[0].im + (R)c2 * a1.im + (R)c1 * a2.im};
-    const cpx<R> j1 = times_dir_i<R, DIR>(cpx<R>{(R)s1 * b1.re + (R)s2 * b2.re, (R)s1 * b1.im + (R)s2 * b2.im});
-    const cpx<R> j2 = times_dir_i<R, DIR>(cpx<R>{(R)s2 * b1.re - (R)s1 * b2.re, (R)s2 * b1.im - (R)s1 * b2.im});
-    v[0] = cadd(v[0], cadd(a1, a2));
-    v[1] = cadd(m1, j1);
-    v[4] = csub(m1, j1);
-    v[2] = cadd(m2, j2);
-    v[3] = csub(m2, j2);
-  }
-}
-
-// first factor of a stage radix: the DFT of length RAD = F·(RAD/F) runs as RAD/F
-// DFTs of length F, fixed roots, then F DFTs of length RAD/F
-constexpr int radix_first(int r) { return r % 5 == 0 ? 5 : r % 4 == 0 ? 4 : r % 3 == 0 ? 3 : 2; }
-
-template <typename R, int RAD, int DIR>
-__device__ __forceinline__ void dft_radix(cpx<R> (&v)[RAD]) {
-  constexpr int F = radix_first(RAD), G = RAD / F;
-  if constexpr (G == 1) {
-    dft_prime<R, RAD, DIR>(v);
-  } else {
-    // input index t = tf G + tg, output index kf + F kg
-    cpx<R> a[G][F];
-#pragma unroll
-    for (int tg = 0; tg < G; ++tg) {
-      cpx<R> u[F];
-#pragma unroll
-      for (int tf = 0; tf < F; ++tf) u[tf] = v[tf * G + tg];
-      dft_prime<R, F, DIR>(u);
-#pragma unroll
-      for (int kf = 0; kf < F; ++kf) a[tg][kf] = mul_root<R, RAD, DIR>(u[kf], tg * kf);
-    }
-#pragma unroll
-    for (int kf = 0; kf < F; ++kf) {
-      cpx<R> u[G];
-#pragma unroll
-      for (int tg = 0; tg < G; ++tg) u[tg] = a[tg][kf];
-      dft_radix<R, G, DIR>(u);
-#pragma unroll
-      for (int kg = 0; kg < G; ++kg) v[kf + F * kg] = u[kg];
-    }
-  }
-}
 
 // One Stockham stage of radix RAD over the line in buf (element p at
 // buf[gpos(p) << lg]) after ns = the product of the earlier radices.  Twiddles:
@@ -1243,6 +986,10 @@ bool make_gen_plan(int n, int E, int maxthr, GenPlan* gp, int order, int nthr_re
   return false;
 }
 
+// Whether a mixed-radix pass takes the register lines (hp_lines.hip), which have one
+// schedule per length; the other schedules a tuning file may ask for run in LDS.
+static bool line_kernels(const PassTune& t) { return t.order < 1 || t.order >= kGenOrders; }
+
 // A pass's plan with its run-time choices, or the built-in one when they do not fit.
 static bool tuned_gen_plan(int n, int E, int maxthr, const PassTune& t, GenPlan* gp, int smax) {
   if ((t.nthr > 0 || t.order > 0) && make_gen_plan(n, E, maxthr, gp, t.order, t.nthr, smax)) return true;
@@ -1318,6 +1065,16 @@ int tune_candidates(int real_kind, int kind, int n, int S, int mode, int K, Pass
     }
     return cnt;
   }
+  LinePlan lp;
+  const int lk = kind == kTuneRows ? kLineRows : kind == kTuneCombine ? kLineComb : mode == 1 ? kLineSym : kLineCols;
+  if (make_line_plan(real_kind, n, lk, S, K, 0, &lp)) {
+    // register lines: the lines (rows) per workgroup vary
+    for (int tc = 1; tc <= 16; tc *= 2) {
+      LinePlan q;
+      if (make_line_plan(real_kind, n, lk, S, K, tc, &q) && q.L == tc * q.splits) push(PassTune{0, tc, 0, 0});
+    }
+    return cnt;
+  }
   const int E = kind == kTuneRows ? kGenRowE : (real_kind == 0 ? gen_e<double>() : gen_e<float>());
   const int maxthr = kind == kTuneRows ? 512 : (real_kind == 0 ? gen_maxthr<double>() : gen_maxthr<float>());
   const int gk = kind == kTuneRows ? kGenRows : kind == kTuneCols ? (mode == 1 ? kGenSym : kGenCols) : kGenComb;
@@ -1351,12 +1108,6 @@ int tune_candidates(int real_kind, int kind, int n, int S, int mode, int K, Pass
     }
   }
   return cnt;
-}
-
-template <typename K>
-static void allow_dynamic_lds(K kernel, size_t bytes) {
-  // lines longer than 64 KiB of LDS need the limit raised once per kernel
-  if (bytes > 65536) (void)hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
 template <typename R, typename TI>
@@ -1411,9 +1162,6 @@ static hipError_t combine_gen_l(const GenPlan& gp, const CombineArgs& a, hipStre
                      a.Mt, a.mo, gp, (const cpx<R>*)a.tw, a.skip, a.order, a.lag, a.posa, a.Ma);
   return hipGetLastError();
 }
-static int interp_mode(const CombineArgs& a) {
-  return a.order >= 2 ? kInterpLagrange : (a.Ma >= 2 ? kInterpBilinear : kInterpLinear);
-}
 template <typename R, typename TO, bool ACC>
 static hipError_t combine_gen(const GenPlan& gp, const CombineArgs& a, hipStream_t st) {
   switch (interp_mode(a)) {
@@ -1427,6 +1175,9 @@ hipError_t launch_rows_fwd(int real_kind, int in_kind, int n, const void* in, vo
                            size_t in_rs, size_t out_rs, int nrhs, const void* tw, const int* skip,
                            const PassTune& tune, hipStream_t st, const hipEvent_t* tev) {
   if (!is_pow2_len(n)) {
+    LinePlan lp;
+    if (line_kernels(tune) && make_line_plan(real_kind, n, kLineRows, rows, 1, tune.tc, &lp))
+      return launch_line_rows(real_kind, in_kind, lp, in, out, rows, in_rs, out_rs, nrhs, tw, skip, st, tev);
     GenPlan gp;
     if (!tuned_gen_plan(n, kGenRowE, 512, tune, &gp, gen_rows_smax(real_kind, n))) return hipErrorInvalidValue;
     if (real_kind == 0) {
@@ -1486,6 +1237,12 @@ struct ColsL {
 
 hipError_t launch_cols(const ColsArgs& a, hipStream_t st) {
   if (cols_use_gen(a.real_kind, a.n)) {
+    LinePlan lp;
+    if (line_kernels(a.tune) &&
+        make_line_plan(a.real_kind, a.n, a.mode == 1 ? kLineSym : kLineCols, a.S,
+                       a.mode == 1 ? a.K : a.outer * a.nfields, a.tune.tc, &lp) &&
+        (a.mode != 1 || a.store_mask_thr == a.n / lp.r[0]))
+      return launch_line_cols(lp, a, st);
     GenPlan gp;
     if (a.real_kind == 0)
       return make_col_plan<double>(a.n, a.S, a.mode, &gp, a.tune) ? cols_gen<double>(gp, a, st) : hipErrorInvalidValue;
@@ -1576,6 +1333,9 @@ bool combine_splits_ok(int real_kind, int n) {
 
 hipError_t launch_combine(const CombineArgs& a, hipStream_t st) {
   if (!is_pow2_len(a.n)) {
+    LinePlan lp;
+    if (line_kernels(a.tune) && make_line_plan(a.real_kind, a.n, kLineComb, a.rows, a.K, a.tune.tc, &lp))
+      return launch_line_combine(lp, a, st);
     GenPlan gp;
     if (a.real_kind == 0
             ? !tuned_gen_plan(a.n, gen_e<double>(), gen_maxthr<double>(), a.tune, &gp, gen_smax<double>(kGenComb))
@@ -1641,14 +1401,16 @@ int symbol_pass_line_threads(int real_kind, int n) {
   return real_kind == 0 ? sym_line_threads<double>(n) : sym_line_threads<float>(n);
 }
 
-int gen_symbol_line_threads(int real_kind, int n) {
+int gen_symbol_line_threads(int real_kind, int n, int* elems) {
+  const int t = line_symbol_threads(real_kind, n, elems);
+  if (t > 0) return t;
+  *elems = real_kind == 0 ? gen_e<double>() : gen_e<float>();
   GenPlan g;
   const bool ok = real_kind == 0
                       ? make_gen_plan(n, gen_e<double>(), gen_maxthr<double>(), &g, 0, 0, gen_smax<double>(kGenSym))
                       : make_gen_plan(n, gen_e<float>(), gen_maxthr<float>(), &g, 0, 0, gen_smax<float>(kGenSym));
   return ok ? g.nthr : 0;
 }
-int gen_symbol_elems(int real_kind) { return real_kind == 0 ? gen_e<double>() : gen_e<float>(); }
 
 int combine_group_rows(int real_kind, int n) {
   return real_kind == 0 ? group_rows<double>(n) : group_rows<float>(n);
