@@ -34,14 +34,13 @@ __device__ __forceinline__ void xcd_tile(int bx, int by, int gx, int gy, int* ti
   *tile = at - *group * gx;
 }
 
-// 1/x for finite x > 0: hardware reciprocal estimate refined by Newton-Raphson
-// steps r <- r + r (1 - x r) (two in FP64, one in FP32).
+// 1/x for finite x > 0: hardware reciprocal estimate r with residual e = 1 - x r, refined
+// in FP64 (e about 2^-24) by the cubic step r <- r + r (e + e^2), whose own error e^3 is
+// below rounding, in FP32 by one Newton-Raphson step.
 __device__ __forceinline__ double recip(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  double e = __builtin_fma(-x, r, 1.0);
-  r = __builtin_fma(r, e, r);
-  e = __builtin_fma(-x, r, 1.0);
-  return __builtin_fma(r, e, r);
+  const double r = __builtin_amdgcn_rcp(x);
+  const double e = __builtin_fma(-x, r, 1.0);
+  return __builtin_fma(r, __builtin_fma(e, e, e), r);
 }
 __device__ __forceinline__ float recip(float x) {
   float r = __builtin_amdgcn_rcpf(x);
@@ -129,25 +128,46 @@ __device__ __forceinline__ R interp_weight(int ab, R tt, R uu, int n, int ord, c
   return (A == n ? (R)1 - tt : (R)0) + (B == n ? tt : (R)0);
 }
 
-// One spectrum element times the symbol of a node, q = 1 / (A_n - g_n lambda) (the 1/N^d
-// of the inverse transform is already in v).  The denominator is formed in FP64 (it
-// cancels near |xi| = omega/|gamma_n|), then reciprocated in the working precision.
-template <typename R>
-__device__ __forceinline__ cpx<R> symbol_times(cpx<R> v, double lam, const NodeConst& nc) {
-  const double dre = nc.are - nc.gre * lam, dim = nc.aim - nc.gim * lam;
-  const R fr = (R)dre, fi = (R)dim;
-  const R inv = recip(fr * fr + fi * fi);
-  return cmul(v, cpx<R>{fr * inv, -fi * inv});
+// Spectrum elements v (the 1/N^d of the inverse transform already in them) times the
+// symbol of a node, x_s = v_s / (A_n - g_n lambda_s).  The denominator is formed in FP64
+// (it cancels near |xi| = omega/|gamma_n|), then reciprocated in the working precision.
+// A node of real speed has a constant imaginary part (most nodes: 16 of 19 at 16 + 3);
+// SPLIT: such nodes take a loop of their own.
+template <bool SPLIT = true, typename R, int E, int CNT>
+__device__ __forceinline__ void symbol_mul(const cpx<R> (&v)[E], cpx<R> (&x)[CNT], const double (&lam)[E],
+                                           const NodeConst& nc) {
+  static_assert(CNT <= E, "outputs within the elements held");
+  if (SPLIT && nc.gim == 0.0) {
+    const R fi = (R)nc.aim, fi2 = fi * fi;
+#pragma unroll
+    for (int s = 0; s < CNT; ++s) {
+      const R fr = (R)(nc.are - nc.gre * lam[s]);
+      const R inv = recip(fr * fr + fi2);
+      x[s] = cmul(v[s], cpx<R>{fr * inv, -fi * inv});
+    }
+  } else {
+#pragma unroll
+    for (int s = 0; s < CNT; ++s) {
+      const R fr = (R)(nc.are - nc.gre * lam[s]), fi = (R)(nc.aim - nc.gim * lam[s]);
+      const R inv = recip(fr * fr + fi * fi);
+      x[s] = cmul(v[s], cpx<R>{fr * inv, -fi * inv});
+    }
+  }
 }
 
-// What the combine of the mixed-radix lines keeps of a point, and the point's weight on
+// What the combine keeps of a point, and the point's weight on
 // node n.  Piecewise linear: the record p itself; the weight is the hat of width 1 around
 // the node's centre on the record's axis, n for a real node, -(i + 2) for layer node i,
 // and -1 beside its own for the background node mo, where the layer's leg starts (record
 // -(1 + j + t), see decode_pos).  The differences and 1 - |d| are exact in FP64, so the
 // weights are those of decode_pos, without a search or a compare per node.
-template <typename R, int IM>
-struct LinePoint {
+// (FP32 rows above 1024 points keep the select: their combine has no registers left for
+// the FP64 temporaries, 2048^2 mixed 190 us with selects before, 208 with hats, 173 with
+// selects and the reordered loads)
+template <typename R>
+constexpr bool hat_weights(int n) { return sizeof(R) == 8 || n <= 1024; }
+template <typename R, int IM, bool HAT = true>
+struct CombPoint {
   int ab;
   R tt, uu;
   __device__ __forceinline__ void clear() { ab = 0xffff; tt = (R)0; uu = (R)0; }
@@ -160,7 +180,7 @@ struct LinePoint {
 };
 __device__ __forceinline__ double hat(double d) { return __builtin_fmin(__builtin_fmax(1.0 - __builtin_fabs(d), 0.0), 1.0); }
 template <typename R>
-struct LinePoint<R, kInterpLinear> {
+struct CombPoint<R, kInterpLinear, true> {
   double p;
   __device__ __forceinline__ void clear() { p = 1e9; }   // no node is near
   __device__ __forceinline__ void load(double pv, double, int, int, int, int, int, const double*) { p = pv; }

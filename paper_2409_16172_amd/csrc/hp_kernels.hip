@@ -24,9 +24,6 @@ namespace hp {
 #ifndef HP_ROWC_THREADS
 #define HP_ROWC_THREADS 64
 #endif
-#ifndef HP_PREFETCH_C
-#define HP_PREFETCH_C 0
-#endif
 // mixed-radix column and combine passes gather each stage's twiddles into LDS at the
 // start of a workgroup (consecutive butterflies then read consecutive entries); pass A
 // reads the line's table from global memory (one transform per workgroup)
@@ -161,29 +158,6 @@ __global__ __launch_bounds__((RowCfg<R, N>::THREADS)) void k_rows_fwd(const cpx<
 }
 
 // ---------------------------------------------------------------- strided passes
-// Symbol multiply of one node on the elements a thread holds.  The denominator
-// A_n - g_n lambda is formed in FP64 (it cancels near |xi| = omega/|gamma_n|),
-// then reciprocated in the working precision.
-template <typename R, int E>
-__device__ __forceinline__ void symbol_mul(const cpx<R> (&vh)[E], cpx<R> (&x)[E], const double (&lam)[E],
-                                           NodeConst nc, double scale) {
-#pragma unroll
-  for (int s = 0; s < E; ++s) {
-    const double dre = nc.are - nc.gre * lam[s];
-    const double dim = nc.aim - nc.gim * lam[s];
-    cpx<R> q;
-    if constexpr (sizeof(R) == 8) {
-      const double inv = scale * recip(dre * dre + dim * dim);
-      q = {dre * inv, -dim * inv};
-    } else {
-      const float fr = (float)dre, fi = (float)dim;
-      const float inv = (float)scale * recip(fr * fr + fi * fi);
-      q = {fr * inv, -fi * inv};
-    }
-    x[s] = cmul(vh[s], q);
-  }
-}
-
 // The column pass of one workgroup: (bx, by, bz) and (gx, gy) stand for blockIdx
 // and gridDim.
 template <typename R, int N, int MODE>
@@ -238,11 +212,12 @@ __device__ __forceinline__ void cols_body(
   const size_t obase = (MODE == 0 ? (size_t)by * N * S : 0) + c;
   const cpx<TI>* src = in + (size_t)rhs * in_rs + (size_t)fld * in_fs + obase;
   cpx<R>* lg = lds + g;   // the TC columns are interleaved in LDS
-  // Symbol pass: the store masks of all nodes are staged in LDS up front, so that
-  // the node loop issues no global load (waiting for one would also wait for the
+  // Symbol pass: the store masks of this workgroup's nodes are staged in LDS up front, so
+  // that the node loop issues no global load (waiting for one would also wait for the
   // previous node's stores: vector memory operations retire in order).
+  const int n_lo = MODE == 1 ? (int)(((long)by * K) / gy) : 0, n_hi = MODE == 1 ? (int)(((long)(by + 1) * K) / gy) : 0;
   if constexpr (MODE == 1) {
-    for (int i = threadIdx.x; i < K * C::T; i += C::THREADS) smask[i] = store_mask[i];
+    for (int i = n_lo * C::T + (int)threadIdx.x; i < n_hi * C::T; i += C::THREADS) smask[i - n_lo * C::T] = store_mask[i];
     __syncthreads();
   }
   cpx<R> x[C::E];
@@ -263,16 +238,16 @@ __device__ __forceinline__ void cols_body(
     const double lc = act ? lam_in[c] : 0.0;
 #pragma unroll
     for (int s = 0; s < C::E; ++s) {
-      vh[s] = x[s];
+      vh[s] = cscale(x[s], (R)scale);
       lam[s] = lam_ax[j + C::T * s] + lc;
     }
     cpx<R>* dst = out + (size_t)rhs * out_rs + obase;
-    const int n_lo = (int)(((long)by * K) / gy), n_hi = (int)(((long)(by + 1) * K) / gy);
     for (int n = n_lo; n < n_hi; ++n) {
-      symbol_mul<R, C::E>(vh, x, lam, nodes[n], scale);
+      // (2048-point FP64 lines, at 238 registers, lose 3 % to the second loop)
+      symbol_mul<(sizeof(R) == 4 || N <= 1024)>(vh, x, lam, nodes[n]);
       fft_e<R, N, C::E, +1, false, C::TC, false, SWP>(x, lg, j, tw);
       // bit s: some point of axis-0 index j + T*s uses node n (else the row is never read)
-      const uint32_t m = act ? (uint32_t)smask[n * C::T + j] : 0u;
+      const uint32_t m = act ? (uint32_t)smask[(n - n_lo) * C::T + j] : 0u;
 #pragma unroll
       for (int s = 0; s < C::E; ++s)
         if ((m >> s) & 1u) dst[(size_t)n * out_fs + (size_t)(j + C::T * s) * S] = x[s];
@@ -301,14 +276,13 @@ __global__ __launch_bounds__((ColsCfg<R, N, MODE>::THREADS)) void k_cols(
 // chip holds NS times more wavefronts.
 template <typename R, int N>
 constexpr bool combine_splits_fit() {
-  return CombCfg<R, N>::T <= 64 && N >= 128;
+  return CombCfg<R, N>::T <= 64;
 }
 constexpr int kCombineSplits = 4;
-
 template <typename R, int N, int NS>
 constexpr int combine_lds_elems() {
   using C = CombCfg<R, N>;
-  constexpr int XCH = NS * C::LDS, RED = (NS - 1) * C::G * N;
+  constexpr int XCH = NS * C::LDS, RED = NS > 1 ? NS * C::G * N : 1;
   return XCH > RED ? XCH : RED;
 }
 
@@ -335,90 +309,73 @@ __device__ __forceinline__ void rows_combine_body(
   const int row = bx * C::G + g;
   const bool act = row < rows;
   const size_t rbase = (size_t)row * N;
-  int ab[C::E];
-  R tt[C::E], uu[C::E];
-  cpx<R> acc[C::E];
-#pragma unroll
-  for (int s = 0; s < C::E; ++s) {
-    ab[s] = 0xffff;
-    tt[s] = (R)0;
-    uu[s] = (R)0;
-    if (act) {
-      const size_t pi = rbase + j + C::T * s;
-      interp_record<R, IM>(pos[pi], IM == kInterpBilinear ? posa[pi] : 0.0, M, Mt, mo, Ma, ord, slag, ab[s], tt[s],
-                           uu[s]);
-    }
-    acc[s] = {0, 0};
-  }
   const uint64_t mask = grpmask[bx];
   const uint64_t rmask = act ? rowmask[row] : 0ull;
   const cpx<R>* fr = fields + (size_t)rhs * frs + rbase;
   cpx<R>* lg = lds + (sp * C::G + g) * lds_elems<R>(N);
-  // Nodes no point of this group uses are skipped; rows that do not use a node
-  // read zeros (pass B did not write them).  The next used node's row is loaded
-  // while the current one is transformed.
-  auto next_node = [&](int n) {
-    while (n < K && ((mask >> n) & 1ull) == 0) ++n;
-    return n;
-  };
-  // the node after the next NS - 1 used ones (this split's next node)
-  auto split_next = [&](int n) {
-    for (int q = 0; q < NS && n < K; ++q) n = next_node(n + 1);
-    return n;
-  };
-  cpx<R> nx[C::E];
-  int n = next_node(0);
-  for (int q = 0; q < sp && n < K; ++q) n = next_node(n + 1);
-  if (!HP_PREFETCH_C && n < K) {
-    // loaded at the top of the loop instead
-  } else if (n < K) {
-    const bool ld = ((rmask >> n) & 1ull) != 0;
+  // Nodes no point of this group uses are skipped; rows that do not use a node read
+  // zeros (pass B did not write them).
+  uint64_t left = mask;
+  for (int q = 0; q < sp; ++q) left &= left - 1;   // split sp starts at the sp-th used node
+  cpx<R> x[C::E];
+  auto load_row = [&](int n) {
+    const cpx<R>* src = fr + (size_t)n * fs + j;
+    // one row per workgroup: every node of the mask is the row's own
+    if (C::G == 1 || ((rmask >> n) & 1ull) != 0) {
 #pragma unroll
-    for (int s = 0; s < C::E; ++s) nx[s] = ld ? fr[(size_t)n * fs + j + C::T * s] : cpx<R>{0, 0};
-  }
-  for (; n < K;) {
-    cpx<R> x[C::E];
-    const int n2 = NS > 1 ? split_next(n) : next_node(n + 1);
-    if (!HP_PREFETCH_C) {
-      const bool ld = ((rmask >> n) & 1ull) != 0;
-#pragma unroll
-      for (int s = 0; s < C::E; ++s) x[s] = ld ? fr[(size_t)n * fs + j + C::T * s] : cpx<R>{0, 0};
+      for (int s = 0; s < C::E; ++s) x[s] = src[C::T * s];
     } else {
 #pragma unroll
-      for (int s = 0; s < C::E; ++s) x[s] = nx[s];
+      for (int s = 0; s < C::E; ++s) x[s] = {0, 0};
     }
-    if (HP_PREFETCH_C && n2 < K) {
-      const bool ld = ((rmask >> n2) & 1ull) != 0;
+  };
+  // the first node's row and the points' records in one memory latency
+  if (left != 0) load_row(__builtin_ctzll(left));
+  CombPoint<R, IM, hat_weights<R>(N)> pt[C::E];
+  cpx<R> acc[C::E];
 #pragma unroll
-      for (int s = 0; s < C::E; ++s) nx[s] = ld ? fr[(size_t)n2 * fs + j + C::T * s] : cpx<R>{0, 0};
+  for (int s = 0; s < C::E; ++s) {
+    pt[s].clear();
+    if (act) {
+      const size_t pi = rbase + j + C::T * s;
+      pt[s].load(pos[pi], IM == kInterpBilinear ? posa[pi] : 0.0, M, Mt, mo, Ma, ord, slag);
     }
+    acc[s] = {0, 0};
+  }
+  while (left != 0) {
+    const int n = __builtin_ctzll(left);
+#pragma unroll
+    for (int q = 0; q < NS; ++q) left &= left - 1;   // 0 stays 0
     fft_e<R, N, C::E, +1, true, 1, false, SWP>(x, lg, j, tw);
 #pragma unroll
     for (int s = 0; s < C::E; ++s) {
-      const R w = interp_weight<R, IM>(ab[s], tt[s], uu[s], n, ord, slag);
+      const R w = pt[s].weight(n, M, mo, ord, slag);
       acc[s].re += w * x[s].re;
       acc[s].im += w * x[s].im;
     }
-    n = n2;
+    if (left != 0) load_row(__builtin_ctzll(left));
   }
-  if constexpr (NS > 1) {   // partial sums of the splits, added by split 0 in a fixed order
+  if constexpr (NS > 1) {
+    // the splits' partial sums meet in LDS; every thread adds some points' NS terms in
+    // split order and stores them
     __syncthreads();        // every split is done with its exchange area
-    if (sp > 0) {
 #pragma unroll
-      for (int s = 0; s < C::E; ++s) lds[((sp - 1) * C::G + g) * N + j + C::T * s] = acc[s];
-    }
+    for (int s = 0; s < C::E; ++s) lds[(sp * C::G + g) * N + j + C::T * s] = acc[s];
     __syncthreads();
-    if (sp > 0) return;
-    for (int q = 1; q < NS; ++q) {
+    const size_t first = (size_t)bx * C::G * N, all = (size_t)rows * N;
+    cpx<TO>* dst = out + (size_t)rhs * out_rs + first;
+    for (int i = threadIdx.x; i < C::G * N && first + i < all; i += C::THREADS * NS) {
+      cpx<R> sum = lds[i];
 #pragma unroll
-      for (int s = 0; s < C::E; ++s) {
-        const cpx<R> o = lds[((q - 1) * C::G + g) * N + j + C::T * s];
-        acc[s].re += o.re;
-        acc[s].im += o.im;
+      for (int q = 1; q < NS; ++q) sum = cadd(sum, lds[q * C::G * N + i]);
+      if constexpr (ACC) {
+        const cpx<TO> o = dst[i];
+        dst[i] = {o.re + (TO)sum.re, o.im + (TO)sum.im};
+      } else {
+        dst[i] = cvt<TO>(sum);
       }
     }
-  }
-  if (act) {
+  } else if (act) {
     cpx<TO>* dst = out + (size_t)rhs * out_rs + rbase;
 #pragma unroll
     for (int s = 0; s < C::E; ++s) {
@@ -433,7 +390,7 @@ __device__ __forceinline__ void rows_combine_body(
 }
 
 template <typename R, typename TO, int N, bool ACC, int IM, int NS = 1>
-__global__ __launch_bounds__((CombCfg<R, N>::THREADS * NS)) void k_rows_combine(
+__global__ __launch_bounds__((CombCfg<R, N>::THREADS * NS)) __attribute__((amdgpu_waves_per_eu(2))) void k_rows_combine(
     const cpx<R>* __restrict__ fields, size_t fs, size_t frs, const double* __restrict__ pos,
     const uint64_t* __restrict__ grpmask, const uint64_t* __restrict__ rowmask, cpx<TO>* __restrict__ out,
     size_t out_rs, int rows, int K, int M, int Mt, int mo, const cpx<R>* __restrict__ tw,
@@ -486,15 +443,12 @@ __device__ __forceinline__ void comb_wave_body(
   const int row = bx * WR + wv;
   if (row >= rows) return;   // no workgroup barrier follows
   const size_t rbase = (size_t)row * N;
-  int ab[E];
-  R tt[E], uu[E];
+  CombPoint<R, IM, hat_weights<R>(N)> pt[E];
   cpx<R> acc[E];
 #pragma unroll
   for (int s = 0; s < E; ++s) {
     const size_t pi = rbase + j + 64 * s;
-    uu[s] = (R)0;
-    interp_record<R, IM>(pos[pi], IM == kInterpBilinear ? posa[pi] : 0.0, M, Mt, mo, Ma, ord, slag, ab[s], tt[s],
-                         uu[s]);
+    pt[s].load(pos[pi], IM == kInterpBilinear ? posa[pi] : 0.0, M, Mt, mo, Ma, ord, slag);
     acc[s] = {0, 0};
   }
   cpx<R>* lw = lds + wv * WaveLine<R, N>::LDS;
@@ -509,7 +463,7 @@ __device__ __forceinline__ void comb_wave_body(
     fft_e<R, N, E, +1, true, 1, true>(x, lw, j, tw);
 #pragma unroll
     for (int s = 0; s < E; ++s) {
-      const R w = interp_weight<R, IM>(ab[s], tt[s], uu[s], n, ord, slag);
+      const R w = pt[s].weight(n, M, mo, ord, slag);
       acc[s].re += w * x[s].re;
       acc[s].im += w * x[s].im;
     }
@@ -1283,6 +1237,22 @@ struct CombineL {
   struct F {
     static hipError_t run(const CombineArgs& a, hipStream_t st) {
       using C = CombCfg<R, N>;
+      dim3 grid((a.rows + C::G - 1) / C::G, a.nrhs);
+      if constexpr (combine_splits_fit<R, N>()) {
+        // node splits while the row groups' wavefronts leave the chip idle, or as tuned
+        // (the tuner's node-group field): 64^2 FP64 13.2 -> 8.4 us, 512^2 FP64 29.5 ->
+        // 19.4, 512^2 FP32 25.0 -> 18.2; eight splits gave 7.9, 27.6 and 19.0.  The
+        // choice depends on the plan only, so that a batch sums in the order a single
+        // field does.
+        const int groups = (int)grid.x;
+        const int ns = a.tune.ng > 0 ? a.tune.ng
+                       : (groups <= 256 && a.K >= 3) || (groups <= 1024 && a.K >= 8) ? kCombineSplits
+                                                                                      : 1;
+        if (ns == kCombineSplits) {
+          combine_launch<R, TO, N, ACC, kCombineSplits>(a, grid, st);
+          return hipGetLastError();
+        }
+      }
       if constexpr (wave_line_fits<R, N>() && (HP_WAVE_COMB & (sizeof(R) == 8 ? 2 : 1)) != 0) {
         const dim3 wgrid((a.rows + kWaveRows - 1) / kWaveRows, a.nrhs);
         switch (interp_mode(a)) {
@@ -1303,33 +1273,13 @@ struct CombineL {
         }
         return hipGetLastError();
       }
-      dim3 grid((a.rows + C::G - 1) / C::G, a.nrhs);
-      if constexpr (combine_splits_fit<R, N>()) {
-        // node splits when the row groups alone would leave most of the chip idle, or
-        // as tuned (the tuner's node-group field: 1 or kCombineSplits).  The choice
-        // depends on the grid only, so that a batch sums in the order a single field does.
-        const int groups = (int)grid.x;
-        const int ns = a.tune.ng > 0 ? a.tune.ng : (groups < 512 ? kCombineSplits : 1);
-        if (ns == kCombineSplits) {
-          combine_launch<R, TO, N, ACC, kCombineSplits>(a, grid, st);
-          return hipGetLastError();
-        }
-      }
       combine_launch<R, TO, N, ACC, 1>(a, grid, st);
       return hipGetLastError();
     }
   };
 };
 
-bool combine_splits_ok(int real_kind, int n) {
-  switch (n) {
-    case 128: return real_kind == 0 ? combine_splits_fit<double, 128>() : combine_splits_fit<float, 128>();
-    case 256: return real_kind == 0 ? combine_splits_fit<double, 256>() : combine_splits_fit<float, 256>();
-    case 512: return real_kind == 0 ? combine_splits_fit<double, 512>() : combine_splits_fit<float, 512>();
-    case 1024: return real_kind == 0 ? combine_splits_fit<double, 1024>() : combine_splits_fit<float, 1024>();
-    default: return false;
-  }
-}
+bool combine_splits_ok(int real_kind, int n) { return is_pow2_len(n) && n <= (real_kind == 0 ? 64 * HP_E64 : 64 * HP_E32); }
 
 hipError_t launch_combine(const CombineArgs& a, hipStream_t st) {
   if (!is_pow2_len(a.n)) {

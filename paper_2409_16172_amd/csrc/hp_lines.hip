@@ -258,8 +258,7 @@ struct SymCtx {
 #pragma unroll
       for (int t = 0; t < RAD; ++t) v[t] = src[t * in_step];
     } else if constexpr (RAD <= E) {
-#pragma unroll
-      for (int t = 0; t < RAD; ++t) v[t] = symbol_times(vh[t], lam[t], nc);
+      symbol_mul(vh, v, lam, nc);
     }
   }
   template <int DIR, int RAD>
@@ -329,7 +328,7 @@ __global__ __launch_bounds__(kLineMaxThr) HP_LINE_WAVES(R, RM, kLineSym) void k_
 template <typename R, int IM, int RM>
 struct CombCtx {
   static constexpr int E = line_spectrum_max<R, RM>();
-  LinePoint<R, IM> pt[E];
+  CombPoint<R, IM> pt[E];
   cpx<R> acc[E];
   const cpx<R>* src;
   size_t in_step;
