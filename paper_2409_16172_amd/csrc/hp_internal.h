@@ -52,6 +52,11 @@ struct KState {
 constexpr int kRedThreads = HP_RED_THREADS;  // threads per block of the reduction kernels
 constexpr int kRedBlocks = HP_RED_BLOCKS;    // blocks per right-hand side (fixed: deterministic sums)
 constexpr int kPartSlots = 2 * kMaxRestart + 4;
+// Blocks of the Arnoldi sweep over npts points (partials stay kRedBlocks apart): half of
+// them up to 2^16 points, whose blocks then still hold at most 256 points.
+__host__ __device__ constexpr int sweep_blocks(size_t npts) {
+  return npts <= ((size_t)1 << 16) ? kRedBlocks / 2 : kRedBlocks;
+}
 
 // Mixed-radix lines (N = 2^a 3^b 5^c, not a power of two): stage radices in
 // order, threads per line and (column passes) lines per workgroup.  A thread

@@ -1500,14 +1500,19 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// Sum the kRedBlocks block partials of `cnt` slots of right-hand side `rhs`
+// Element-wise load of a complex value (keeps a conditional struct copy from
+// becoming a private-memory temporary).
+__device__ __forceinline__ cpx<double> ldc(const cpx<double>& p) { return {p.re, p.im}; }
+
+// Sum the nb (a multiple of 64, at most kRedBlocks) block partials of `cnt` slots of right-hand side `rhs`
 // into sums[] in a fixed order (wave w handles slots w, w + nw, ...; kSlotsPerWave
 // slots per round, so that each lane has 16 partial loads of a round in flight
 // before the first add).
 static_assert(kRedBlocks % 64 == 0, "partials per slot must fill whole wavefronts");
 constexpr int kSlotLoads = kRedBlocks / 64;
 constexpr int kSlotsPerWave = kSlotLoads >= 16 ? 1 : 16 / kSlotLoads;
-__device__ __forceinline__ void reduce_slots(const cpx<double>* __restrict__ part, int rhs, int cnt, cpx<double>* sums) {
+__device__ __forceinline__ void reduce_slots(const cpx<double>* __restrict__ part, int rhs, int cnt, cpx<double>* sums,
+                                             int nb = kRedBlocks) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
   const cpx<double>* pr = part + (size_t)rhs * kPartSlots * kRedBlocks + lane;
   for (int s0 = wv; s0 < cnt; s0 += kSlotsPerWave * nw) {
@@ -1517,7 +1522,7 @@ __device__ __forceinline__ void reduce_slots(const cpx<double>* __restrict__ par
       const int sl = s0 + q * nw;
       const cpx<double>* p = pr + (size_t)(sl < cnt ? sl : s0) * kRedBlocks;
 #pragma unroll
-      for (int b = 0; b < kSlotLoads; ++b) x[q][b] = p[64 * b];
+      for (int b = 0; b < kSlotLoads; ++b) x[q][b] = 64 * b < nb ? ldc(p[64 * b]) : cpx<double>{0.0, 0.0};
     }
 #pragma unroll
     for (int q = 0; q < kSlotsPerWave; ++q) {
@@ -1744,10 +1749,6 @@ __global__ __launch_bounds__(256) void k_scale_v0(cpx<double>* V, size_t npts, s
 // and w = A u_j (slot j+1).  Partial-sum slots: [0, j) a = V^H u_j,
 // [j, 2j) b = V^H w, 2j ||u_j||^2, 2j+1 u_j^H w, 2j+2 ||w||^2.
 
-// Element-wise load of a complex value (keeps a conditional struct copy from
-// becoming a private-memory temporary).
-__device__ __forceinline__ cpx<double> ldc(const cpx<double>& p) { return {p.re, p.im}; }
-
 // Hessenberg columns 0..j-2 staged in LDS, packed: column i (entries 0..i+1) at
 // offset i (i + 3) / 2.
 __device__ __forceinline__ int hpacked(int i) { return i * (i + 3) / 2; }
@@ -1756,7 +1757,7 @@ constexpr int kFinThreads = 1024;
 constexpr int kHPrefetch = ((kMaxRestart - 1) * (kMaxRestart + 1) + kFinThreads - 1) / kFinThreads;
 
 __device__ __forceinline__ void arnoldi_finalize(KState& S, const cpx<double>* part, int rhs, int j, int restart,
-                                                 int* skip_step, int* host_stop) {
+                                                 int* skip_step, int* host_stop, int nb) {
   __shared__ cpx<double> sums[kPartSlots];
   __shared__ cpx<double> zz[kMaxRestart + 1], hp[kMaxRestart + 1], raw[kMaxRestart + 2];
   __shared__ cpx<double> hsh[kHPacked];
@@ -1784,7 +1785,7 @@ __device__ __forceinline__ void arnoldi_finalize(KState& S, const cpx<double>* p
   }
   const double target = S.target;
   int iters = S.iters;
-  reduce_slots(part, rhs, 2 * j + 3, sums);   // ends with a barrier
+  reduce_slots(part, rhs, 2 * j + 3, sums, nb);   // ends with a barrier
   if (t < kMaxRestart) { L.cs[t] = rc; L.sn[t] = rs; }
   if (t <= kMaxRestart) { L.g[t] = rg; hp[t] = rh; }
 #pragma unroll
@@ -1926,7 +1927,7 @@ __device__ __forceinline__ void arnoldi_finalize(KState& S, const cpx<double>* p
 }
 
 // Block b of a right-hand side owns the contiguous point range
-// [b*range, (b+1)*range), range = ceil(npts / kRedBlocks), and walks it in tiles
+// [b*range, (b+1)*range), range = ceil(npts / sweep_blocks), and walks it in tiles
 // of kDotsTile points: u_j and w of the tile are staged in LDS once (their norms
 // and u_j^H w accumulated on the way), then wave q streams the basis vectors
 // q, q + NW, q + 2 NW, ... over the tile, kDotsBatch loads in flight per lane,
@@ -1935,6 +1936,12 @@ __device__ __forceinline__ void arnoldi_finalize(KState& S, const cpx<double>* p
 constexpr int kDotsTile = 1024;
 constexpr int kDotsBatch = 8;
 constexpr int kDotsSlots = 8;   // basis vectors per wave: j <= NW * kDotsSlots
+// Grids whose blocks hold at most 64 SP points keep all of them, of four basis vectors at
+// once, in flight (SP = 4; one memory latency for four vectors instead of one each: 256^2
+// FP64 sweep at j = 28, 19.4 -> 13.5 us).  A kernel of its own: those registers would cost
+// the larger grids a wave per SIMD.
+constexpr int kDotsShort = 4;
+static bool sweep_short(size_t npts) { return npts <= (size_t)sweep_blocks(npts) * 64 * kDotsShort; }
 
 // Where the sweep takes w = A u_j from: the stored vector (slot j+1), or, fused
 // with the right-preconditioned step, the stencil applied to z = Q u_j as each
@@ -1960,14 +1967,15 @@ struct WStencil {
 
 // The sweep of one block over its range of one right-hand side's basis Vr; pr:
 // this block's partial-sum column.
-template <int NW, typename WSrc>
+template <int NW, int SP, typename WSrc>
 __device__ __forceinline__ void arnoldi_dots_body(const cpx<double>* Vr, size_t npts, cpx<double>* pr, int j,
                                                   const WSrc& wsrc, int bx) {
   __shared__ cpx<double> su[kDotsTile], sw[kDotsTile];
   __shared__ double red[NW][6];
   const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
   const cpx<double>* U = Vr + (size_t)j * npts;
-  const size_t range = (npts + kRedBlocks - 1) / kRedBlocks;
+  const int nb = sweep_blocks(npts);
+  const size_t range = (npts + nb - 1) / nb;
   const size_t r0 = (size_t)bx * range;
   const size_t r1 = r0 + range < npts ? r0 + range : npts;
   cpx<double> acc[2 * kDotsSlots];
@@ -1986,6 +1994,42 @@ __device__ __forceinline__ void arnoldi_dots_body(const cpx<double>* Vr, size_t 
       ww += w.re * w.re + w.im * w.im;
     }
     __syncthreads();
+    if constexpr (SP > 0) {   // the tile's points of PAIR vectors at once
+      constexpr int PAIR = 4;
+#pragma unroll
+      for (int s0 = 0; s0 < kDotsSlots; s0 += PAIR) {
+        if (q + NW * s0 >= j) break;
+        cpx<double> x[PAIR][SP];
+#pragma unroll
+        for (int u = 0; u < PAIR; ++u) {
+          const int k = q + NW * (s0 + u);
+          const cpx<double>* vk = Vr + (size_t)(k < j ? k : j - 1) * npts + t0;
+#pragma unroll
+          for (int b = 0; b < SP; ++b) {
+            const int p = lane + 64 * b;
+            x[u][b] = p < n ? ldc(vk[p]) : cpx<double>{0.0, 0.0};
+          }
+        }
+#pragma unroll
+        for (int b = 0; b < SP; ++b) {
+          int p = lane + 64 * b;
+          p = p < n ? p : 0;   // x is zero there
+          const cpx<double> u0 = su[p], w0 = sw[p];
+#pragma unroll
+          for (int u = 0; u < PAIR; ++u) {   // past v_{j-1} the sums are not stored
+            const cpx<double> v = x[u][b];
+            cpx<double>& a = acc[2 * (s0 + u)];
+            cpx<double>& c = acc[2 * (s0 + u) + 1];
+            a.re += v.re * u0.re + v.im * u0.im;     // conj(v) u
+            a.im += v.re * u0.im - v.im * u0.re;
+            c.re += v.re * w0.re + v.im * w0.im;     // conj(v) w
+            c.im += v.re * w0.im - v.im * w0.re;
+          }
+        }
+      }
+      __syncthreads();
+      continue;
+    }
 #pragma unroll
     for (int sl = 0; sl < kDotsSlots; ++sl) {
       const int k = q + NW * sl;
@@ -2046,18 +2090,18 @@ __device__ __forceinline__ void arnoldi_dots_body(const cpx<double>* Vr, size_t 
   }
 }
 
-template <int NW>
+template <int NW, int SP>
 __global__ __launch_bounds__(NW * 64) void k_arnoldi_dots(const cpx<double>* __restrict__ V, size_t npts,
                                                           size_t vrs, cpx<double>* __restrict__ part,
                                                           const int* __restrict__ skip_step, int j) {
   const int rhs = blockIdx.y;
   if (skip_step[rhs]) return;
   const cpx<double>* Vr = V + (size_t)rhs * vrs;
-  arnoldi_dots_body<NW>(Vr, npts, part + (size_t)rhs * kPartSlots * kRedBlocks + blockIdx.x, j,
+  arnoldi_dots_body<NW, SP>(Vr, npts, part + (size_t)rhs * kPartSlots * kRedBlocks + blockIdx.x, j,
                         WStored{Vr + (size_t)(j + 1) * npts}, blockIdx.x);
 }
 
-template <int NW, typename R, typename TI, int DIM>
+template <int NW, int SP, typename R, typename TI, int DIM>
 __global__ __launch_bounds__(NW * 64) void k_arnoldi_dots_st(cpx<double>* V, size_t npts, size_t vrs,
                                                              cpx<double>* __restrict__ part,
                                                              const int* __restrict__ skip_step, int j,
@@ -2067,16 +2111,17 @@ __global__ __launch_bounds__(NW * 64) void k_arnoldi_dots_st(cpx<double>* V, siz
   const int rhs = blockIdx.y;
   if (skip_step[rhs]) return;
   cpx<double>* Vr = V + (size_t)rhs * vrs;
-  arnoldi_dots_body<NW>(Vr, npts, part + (size_t)rhs * kPartSlots * kRedBlocks + blockIdx.x, j,
+  arnoldi_dots_body<NW, SP>(Vr, npts, part + (size_t)rhs * kPartSlots * kRedBlocks + blockIdx.x, j,
                         WStencil<R, TI, DIM>{z + (size_t)rhs * z_rs, coef, Vr + (size_t)(j + 1) * npts, n0, n1,
                                              n2, ih0, ih1, ih2}, blockIdx.x);
 }
 
 __global__ __launch_bounds__(kFinThreads) void k_arnoldi_fin(const cpx<double>* __restrict__ part, int* __restrict__ skip_step,
-                                                      KState* state, int j, int restart, int* __restrict__ host_stop) {
+                                                      KState* state, int j, int restart, int* __restrict__ host_stop,
+                                                      int nb) {
   const int rhs = blockIdx.x;
   if (skip_step[rhs]) return;
-  arnoldi_finalize(state[rhs], part, rhs, j, restart, skip_step, host_stop);
+  arnoldi_finalize(state[rhs], part, rhs, j, restart, skip_step, host_stop, nb);
 }
 
 // slot j <- v_j = (u_j - V a) / sigma ; slot j+1 <- u_{j+1} = w / sigma - V cv - cu u_j.
@@ -2159,6 +2204,54 @@ __global__ __launch_bounds__(256) void k_arnoldi_update(cpx<double>* __restrict_
   }
 }
 
+// The same on grids of 4096 to 2^18 points: one point per thread and eight vectors in
+// flight, so that the launch has four times the workgroups and half the rounds of memory
+// latency (256^2 FP64 at j = 28: 10.0 -> 5.1 us).  Smaller grids keep the kernel above:
+// where its last workgroup's points round differently, a solve whose source and medium
+// are mirror images of themselves does not stay in the symmetric subspace, as the
+// oracle's does not (36^2 plain GMRES(64): 112 steps with either, 107 in exact symmetry).
+constexpr size_t kUpdSmallMin = 4096, kUpdSmallMax = (size_t)1 << 18;
+constexpr int kUpdSmallChunk = 8;
+__global__ __launch_bounds__(256) void k_arnoldi_update_small(cpx<double>* __restrict__ V, size_t npts, size_t vrs,
+                                                              const KState* __restrict__ state,
+                                                              const int* __restrict__ skip_step, int j) {
+  __shared__ cpx<double> ca[kMaxRestart + kUpdSmallChunk], cc[kMaxRestart + kUpdSmallChunk];
+  const int rhs = blockIdx.y;
+  const KState& S = state[rhs];
+  if (skip_step[rhs] && S.stop_at != j) return;
+  for (int i = threadIdx.x; i < kMaxRestart + kUpdSmallChunk; i += blockDim.x) {
+    ca[i] = i < j ? S.av[i] : cpx<double>{0.0, 0.0};
+    cc[i] = i < j ? S.cv[i] : cpx<double>{0.0, 0.0};
+  }
+  __syncthreads();
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= npts) return;
+  cpx<double>* Vr = V + (size_t)rhs * vrs;
+  cpx<double>* U = Vr + (size_t)j * npts;
+  cpx<double>* W = Vr + (size_t)(j + 1) * npts;
+  const cpx<double> u = U[i], w = W[i], cu = S.cu;   // with the first basis loads
+  const double isg = S.inv_sigma;
+  cpx<double> sa = {0.0, 0.0}, sc = {0.0, 0.0};
+  for (int v0 = 0; v0 < j; v0 += kUpdSmallChunk) {
+    cpx<double> x[kUpdSmallChunk];
+#pragma unroll
+    for (int t = 0; t < kUpdSmallChunk; ++t) {
+      const int k = v0 + t < j ? v0 + t : j - 1;   // past v_{j-1} the coefficient is zero
+      x[t] = Vr[(size_t)k * npts + i];
+    }
+#pragma unroll
+    for (int t = 0; t < kUpdSmallChunk; ++t) {
+      const cpx<double> a = ca[v0 + t], c = cc[v0 + t];
+      sa.re += a.re * x[t].re - a.im * x[t].im;
+      sa.im += a.re * x[t].im + a.im * x[t].re;
+      sc.re += c.re * x[t].re - c.im * x[t].im;
+      sc.im += c.re * x[t].im + c.im * x[t].re;
+    }
+  }
+  const cpx<double> cuu = cmul(cu, u);
+  U[i] = cscale(csub(u, sa), isg);
+  W[i] = {w.re * isg - sc.re - cuu.re, w.im * isg - sc.im - cuu.im};
+}
 
 // The update for FP64 2-D grids whose rows (512 to 2048 points) run the register
 // transform: each workgroup updates whole rows of v_j and u_{j+1} (the same sums in
@@ -2583,47 +2676,47 @@ hipError_t launch_scale_v0(const KrylovArgs& a, hipStream_t st) {
 }
 
 hipError_t launch_arnoldi_dots(const KrylovArgs& a, int j, hipStream_t st) {
-  // four waves per block when there are 512 or more blocks per right-hand side
-  // (two blocks per CU), else eight
-  if (kRedBlocks >= 512 && j <= 4 * kDotsSlots)
-    hipLaunchKernelGGL(k_arnoldi_dots<4>, dim3(kRedBlocks, a.nrhs), dim3(4 * 64), 0, st, a.V, a.npts, a.vrs,
-                       a.part, (const int*)a.skip_step, j);
-  else if (j <= 8 * kDotsSlots)
-    hipLaunchKernelGGL(k_arnoldi_dots<8>, dim3(kRedBlocks, a.nrhs), dim3(8 * 64), 0, st, a.V, a.npts, a.vrs,
-                       a.part, (const int*)a.skip_step, j);
-  else
-    return hipErrorInvalidValue;
+  // four waves per block (two blocks per CU) while the slots suffice, else eight
+  const dim3 grid(sweep_blocks(a.npts), a.nrhs);
+  auto go = [&](auto kern, int nw) {
+    hipLaunchKernelGGL(kern, grid, dim3(nw * 64), 0, st, a.V, a.npts, a.vrs, a.part, (const int*)a.skip_step, j);
+  };
+  if (j > 8 * kDotsSlots) return hipErrorInvalidValue;
+  if (j > 4 * kDotsSlots) go(k_arnoldi_dots<8, 0>, 8);
+  else if (sweep_short(a.npts)) go(k_arnoldi_dots<4, kDotsShort>, 4);
+  else go(k_arnoldi_dots<4, 0>, 4);
   hipLaunchKernelGGL(k_arnoldi_fin, dim3(a.nrhs), dim3(kFinThreads), 0, st, (const cpx<double>*)a.part, a.skip_step,
-                     a.state, j, a.restart, a.host_stop);
+                     a.state, j, a.restart, a.host_stop, sweep_blocks(a.npts));
   return hipGetLastError();
 }
 
-template <int NW, typename R, typename TI, int DIM>
+template <int NW, int SP, typename R, typename TI, int DIM>
 static void dots_st_launch(const KrylovArgs& a, int j, const StencilArgs& s, hipStream_t st) {
-  hipLaunchKernelGGL((k_arnoldi_dots_st<NW, R, TI, DIM>), dim3(kRedBlocks, a.nrhs), dim3(NW * 64), 0, st, a.V,
+  hipLaunchKernelGGL((k_arnoldi_dots_st<NW, SP, R, TI, DIM>), dim3(sweep_blocks(a.npts), a.nrhs), dim3(NW * 64), 0, st, a.V,
                      a.npts, a.vrs, a.part, (const int*)a.skip_step, j, (const cpx<TI>*)s.u, s.u_rs,
                      (const cpx<R>*)s.coef, s.n[0], s.n[1], s.dim == 3 ? s.n[2] : 1, (R)s.ih2[0], (R)s.ih2[1],
                      (R)s.ih2[2]);
 }
 
-template <int NW>
+template <int NW, int SP>
 static hipError_t dots_st_dispatch(const KrylovArgs& a, int j, const StencilArgs& s, hipStream_t st) {
-  if (s.kind == 0 && s.dim == 2) dots_st_launch<NW, double, double, 2>(a, j, s, st);
-  else if (s.kind == 0 && s.dim == 3) dots_st_launch<NW, double, double, 3>(a, j, s, st);
-  else if (s.kind == 2 && s.dim == 2) dots_st_launch<NW, float, float, 2>(a, j, s, st);
-  else if (s.kind == 2 && s.dim == 3) dots_st_launch<NW, float, float, 3>(a, j, s, st);
+  if (s.kind == 0 && s.dim == 2) dots_st_launch<NW, SP, double, double, 2>(a, j, s, st);
+  else if (s.kind == 0 && s.dim == 3) dots_st_launch<NW, SP, double, double, 3>(a, j, s, st);
+  else if (s.kind == 2 && s.dim == 2) dots_st_launch<NW, SP, float, float, 2>(a, j, s, st);
+  else if (s.kind == 2 && s.dim == 3) dots_st_launch<NW, SP, float, float, 3>(a, j, s, st);
   else return hipErrorInvalidValue;
   return hipSuccess;
 }
 
 hipError_t launch_arnoldi_dots_stencil(const KrylovArgs& a, int j, const StencilArgs& s, hipStream_t st) {
   hipError_t e;
-  if (kRedBlocks >= 512 && j <= 4 * kDotsSlots) e = dots_st_dispatch<4>(a, j, s, st);
-  else if (j <= 8 * kDotsSlots) e = dots_st_dispatch<8>(a, j, s, st);
-  else return hipErrorInvalidValue;
+  if (j > 8 * kDotsSlots) return hipErrorInvalidValue;
+  if (j > 4 * kDotsSlots) e = dots_st_dispatch<8, 0>(a, j, s, st);
+  else if (sweep_short(a.npts)) e = dots_st_dispatch<4, kDotsShort>(a, j, s, st);
+  else e = dots_st_dispatch<4, 0>(a, j, s, st);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_arnoldi_fin, dim3(a.nrhs), dim3(kFinThreads), 0, st, (const cpx<double>*)a.part, a.skip_step,
-                     a.state, j, a.restart, a.host_stop);
+                     a.state, j, a.restart, a.host_stop, sweep_blocks(a.npts));
   return hipGetLastError();
 }
 
@@ -2650,6 +2743,11 @@ hipError_t launch_arnoldi_update_rows(const KrylovArgs& a, int j, void* t, int n
 }
 
 hipError_t launch_arnoldi_update(const KrylovArgs& a, int j, hipStream_t st) {
+  if (a.npts >= kUpdSmallMin && a.npts < kUpdSmallMax) {
+    hipLaunchKernelGGL(k_arnoldi_update_small, dim3((unsigned)((a.npts + 255) / 256), a.nrhs), dim3(256), 0, st, a.V,
+                       a.npts, a.vrs, a.state, a.skip_step, j);
+    return hipGetLastError();
+  }
   const size_t ub = (a.npts + 256 * kUpdPts - 1) / (256 * kUpdPts);
   hipLaunchKernelGGL(k_arnoldi_update, dim3((unsigned)(ub < 1024 ? ub : 1024), a.nrhs), dim3(256), 0, st, a.V, a.npts, a.vrs,
                      a.state, a.skip_step, j);
@@ -2859,7 +2957,7 @@ __global__ __launch_bounds__(4 * 64) void k_group_dots(const GroupArgs<GDotsDesc
   const GDotsDesc& d = a.m[group_member_of(a)];
   if (d.skip[0] != 0) return;
   const int bx = (int)blockIdx.x - d.block0;
-  arnoldi_dots_body<4>(d.V, d.npts, d.part + bx, d.j,
+  arnoldi_dots_body<4, 0>(d.V, d.npts, d.part + bx, d.j,
                        WStencilAny{d.z, d.coef, d.V + (size_t)(d.j + 1) * d.npts, d.dim, d.n0, d.n1, d.n2, d.ih0,
                                    d.ih1, d.ih2},
                        bx);
@@ -2870,13 +2968,13 @@ struct GFinDesc {
   int* skip;
   KState* state;
   int* host_stop;
-  int j, restart;
+  int j, restart, nb;
 };
 
 __global__ __launch_bounds__(kFinThreads) void k_group_fin(const GroupArgs<GFinDesc> a) {
   const GFinDesc& d = a.m[blockIdx.x];
   if (d.skip[0] != 0) return;
-  arnoldi_finalize(d.state[0], d.part, 0, d.j, d.restart, d.skip, d.host_stop);
+  arnoldi_finalize(d.state[0], d.part, 0, d.j, d.restart, d.skip, d.host_stop, d.nb);
 }
 
 struct GUpdDesc {
@@ -3052,19 +3150,20 @@ hipError_t launch_group_step(const GroupMember* m, int count, hipStream_t st) {
     GroupArgs<GFinDesc> F{};
     GroupArgs<GUpdDesc> U{};
     D.count = F.count = U.count = count;
-    int ublocks = 0;
+    int ublocks = 0, dblocks = 0;
     for (int q = 0; q < count; ++q) {
       const GroupMember& g = m[q];
       D.m[q] = GDotsDesc{g.V, g.part, g.skip_step, (const cpx<float>*)g.z, (const cpx<float>*)g.coef32, g.npts,
                          (float)g.ih2[0], (float)g.ih2[1], (float)g.ih2[2], g.j, g.dim, g.n[0], g.n[1],
-                         g.dim == 3 ? g.n[2] : 1, q * kRedBlocks};
-      F.m[q] = GFinDesc{g.part, g.skip_step, g.state, g.host_stop, g.j, g.restart};
+                         g.dim == 3 ? g.n[2] : 1, dblocks};
+      dblocks += sweep_blocks(g.npts);
+      F.m[q] = GFinDesc{g.part, g.skip_step, g.state, g.host_stop, g.j, g.restart, sweep_blocks(g.npts)};
       const size_t ub = (g.npts + 256 * kUpdPts - 1) / (256 * kUpdPts);
       const int gx = (int)(ub < 1024 ? ub : 1024);
       U.m[q] = GUpdDesc{g.V, g.state, g.skip_step, g.npts, g.j, gx, ublocks};
       ublocks += gx;
     }
-    hipLaunchKernelGGL(k_group_dots, dim3(count * kRedBlocks), dim3(4 * 64), 0, st, D);
+    hipLaunchKernelGGL(k_group_dots, dim3(dblocks), dim3(4 * 64), 0, st, D);
     hipLaunchKernelGGL(k_group_fin, dim3(count), dim3(kFinThreads), 0, st, F);
     hipLaunchKernelGGL(k_group_update, dim3(ublocks), dim3(256), 0, st, U);
   }
