@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <vector>
+
 #include "../../include/helmpre.h"
 #include "hp_fft.h"
 
@@ -132,7 +134,7 @@ struct LinePlan {
   int K[kLineStages];          // product of the earlier radices
   int J[kLineStages];          // product of the later ones
   int pitch[kLineStages - 1];  // LDS row pitch of the exchange after each stage
-  int slots, twn;              // LDS elements of a line and of the stage tables
+  int slots, twn;              // LDS elements of a line and of the stage table
 };
 // The plan of one pass over lines of length n: `across` of them side by side (rows, or
 // the columns of a slab), `groups` such sets (slabs and fields; node fields of pass B; of
@@ -140,6 +142,10 @@ struct LinePlan {
 // when they do not fit).  False: a length these kernels do not take (powers of two;
 // lengths without at most four radices and kLineMaxThr threads).
 bool make_line_plan(int real_kind, int n, int kind, int across, int groups, int lines_req, LinePlan* out);
+// Stage table of the inverse transforms of pass B (kLineSym) or C (kLineComb): indices into
+// the line's table exp(-2 pi i m / n), stage by stage from the second, entry (t - 1) K + k;
+// returns the count (0: the kernels do not take n).
+int line_stage_table(int real_kind, int n, int kind, std::vector<int>* index);
 // Threads per line whose store masks pass B reads (bit t of thread j: axis-0 index
 // j + threads * t) and the elements each stores; 0 if these kernels do not take n.
 int line_symbol_threads(int real_kind, int n, int* elems);
@@ -180,6 +186,7 @@ struct ColsArgs {
   int S, outer, nfields, nrhs;
   size_t in_rs, out_rs, in_fs, out_fs;
   const void* tw;
+  const void* stw;   // mode 1, register lines: the stage table of line_stage_table
   const int* skip;
   const double* lam_ax;
   const double* lam_in;
@@ -212,6 +219,7 @@ struct CombineArgs {
   size_t out_rs;
   int rows, K, M, Mt, mo, nrhs;
   const void* tw;
+  const void* stw;     // register lines: the stage table of line_stage_table
   const int* skip;
   int order;           // real-axis interpolation degree in effect (1 = piecewise linear)
   const double* lag;   // order >= 2: real nodes [0, kMaxNodes), then for node n and stencil

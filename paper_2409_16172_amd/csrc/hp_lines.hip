@@ -55,8 +55,8 @@ struct LineBuf {
 // and takes part).  The pass's context c fills the inputs of the first stage (in) and
 // takes the outputs of the last (out); it is one struct handed down by reference, with
 // its register arrays as members, so that the compiler keeps them in registers through
-// the radix switches.  tw: this stage's part of the LDS table (TWL), entry (t - 1) K + k, else the
-// line's table exp(-2 pi i m / N) in global memory.
+// the radix switches.  tw: this stage's part of the plan's stage table in LDS (TWL), entry
+// (t - 1) K + k, else the line's table exp(-2 pi i m / N) in global memory.
 template <typename R, int RAD, int DIR, int KIND, bool TWL, typename Ctx>
 __device__ __forceinline__ void line_stage(const LinePlan& p, int s, LineBuf<R>& b, int tl, int mk, bool live,
                                            const cpx<R>* __restrict__ tw, Ctx& c) {
@@ -142,7 +142,8 @@ __device__ __forceinline__ void line_mid_k(const LinePlan& p, int tl, int (&mk)[
   mk[1] = p.nst > 3 ? tl / p.J[2] : 0;
 }
 
-// The transform of one line; every thread of the workgroup calls it together.
+// The transform of one line; every thread of the workgroup calls it together.  TWL: tw is
+// the stage table, else the line's table.
 template <typename R, int DIR, bool TWL, int RM, typename Ctx>
 __device__ __forceinline__ void line_fft(const LinePlan& p, LineBuf<R>& b, int tl, const int (&mk)[2], bool live,
                                          const cpx<R>* __restrict__ tw, Ctx& c) {
@@ -158,17 +159,10 @@ __device__ __forceinline__ void line_fft(const LinePlan& p, LineBuf<R>& b, int t
   if (p.two_buf) b.cur ^= 1;   // the next transform writes the other region
 }
 
-// The stage tables of plan p (p.twn entries) gathered from the line's table.
+// The plan's stage table (p.twn entries) into LDS.
 template <typename R>
-__device__ __forceinline__ void line_tables(const LinePlan& p, cpx<R>* dst, const cpx<R>* __restrict__ tw) {
-  for (int s = 1; s < p.nst; ++s) {
-    const int K = p.K[s], cnt = K * (p.r[s] - 1);
-    for (int q = threadIdx.x; q < cnt; q += blockDim.x) {
-      const int t = q / K + 1, k = q - (t - 1) * K;
-      dst[q] = tw[k * t * p.J[s]];
-    }
-    dst += cnt;
-  }
+__device__ __forceinline__ void line_tables(const LinePlan& p, cpx<R>* dst, const cpx<R>* __restrict__ stw) {
+  for (int q = threadIdx.x; q < p.twn; q += blockDim.x) dst[q] = stw[q];
 }
 
 // Lines read from and written to global memory, elements step apart.
@@ -282,6 +276,7 @@ template <typename R, int RM>
 __global__ __launch_bounds__(kLineMaxThr) HP_LINE_WAVES(R, RM, kLineSym) void k_line_sym(const cpx<R>* __restrict__ in, cpx<R>* __restrict__ out,
                                                           int S, size_t in_rs, size_t out_rs, size_t out_fs,
                                                           LinePlan fw, LinePlan iv, const cpx<R>* __restrict__ tw,
+                                                          const cpx<R>* __restrict__ stw,
                                                           const int* __restrict__ skip,
                                                           const double* __restrict__ lam_ax,
                                                           const double* __restrict__ lam_in,
@@ -299,7 +294,7 @@ __global__ __launch_bounds__(kLineMaxThr) HP_LINE_WAVES(R, RM, kLineSym) void k_
   const int reg = L * fw.slots;
   cpx<R>* tab = lds + reg * (fw.two_buf ? 2 : 1);
   LineBuf<R> b{lds + g, L, reg, 0};
-  line_tables<R>(iv, tab, tw);   // the transform's barriers come before their first use
+  line_tables<R>(iv, tab, stw);   // the transform's barriers come before their first use
   int mk[2];
   line_mid_k(fw, tl, mk);
   const int J0 = iv.J[0], KL = iv.K[iv.nst - 1];
@@ -361,7 +356,7 @@ __global__ __launch_bounds__(kLineMaxThr) HP_LINE_WAVES(R, RM, kLineComb) void k
                                                               const uint64_t* __restrict__ rowmask,
                                                               cpx<TO>* __restrict__ out, size_t out_rs, int rows,
                                                               int M, int Mt, int mo, LinePlan p,
-                                                              const cpx<R>* __restrict__ tw,
+                                                              const cpx<R>* __restrict__ stw,
                                                               const int* __restrict__ skip, int ord,
                                                               const double* __restrict__ lag,
                                                               const double* __restrict__ posa, int Ma) {
@@ -385,7 +380,7 @@ __global__ __launch_bounds__(kLineMaxThr) HP_LINE_WAVES(R, RM, kLineComb) void k
   const int reg = p.L * p.slots;
   cpx<R>* tab = lds + reg * (p.two_buf ? 2 : 1);
   LineBuf<R> b{lds + line * p.slots, 1, reg, 0};
-  line_tables<R>(p, tab, tw);
+  line_tables<R>(p, tab, stw);
   int mk[2];
   line_mid_k(p, tl, mk);
   const int KL = p.K[p.nst - 1], RL = p.r[p.nst - 1];
@@ -406,18 +401,20 @@ __global__ __launch_bounds__(kLineMaxThr) HP_LINE_WAVES(R, RM, kLineComb) void k
     }
     c.acc[t] = {0, 0};
   }
-  uint64_t left = 0;
-  for (int i = 0; i < nrow; ++i) left |= row0 + i < rows ? rowmask[row0 + i] : 0ull;
   const uint64_t rm = live ? rowmask[row] : 0ull;
   if constexpr (SPLIT) {
-    // every line walks its own nodes; all make the same number of transforms
-    const int rounds = ((int)__builtin_popcountll(left) + p.splits - 1) / p.splits;
+    // every line walks its share of its own row's nodes (so that the order of a row's sum
+    // does not depend on the rows beside it); all make the same number of transforms
+    int most = 0;
+    for (int i = 0; i < nrow; ++i)
+      most = max(most, row0 + i < rows ? (int)__builtin_popcountll(rowmask[row0 + i]) : 0);
+    uint64_t left = rm;
     for (int q = 0; q < sp; ++q) left &= left - 1;
-    for (int i = 0; i < rounds; ++i) {
+    for (int i = 0; i < most; i += p.splits) {
       const bool on = left != 0;
       c.n = on ? __builtin_ctzll(left) : 0;
       c.src = fields + (size_t)rhs * frs + (size_t)c.n * fs + rbase;
-      line_fft<R, +1, true, RM>(p, b, tl, mk, live && on && ((rm >> c.n) & 1ull) != 0, tab, c);
+      line_fft<R, +1, true, RM>(p, b, tl, mk, on, tab, c);
       for (int q = 0; q < p.splits; ++q) left &= left - 1;   // 0 stays 0
     }
     // the splits' sums, added by the first in a fixed order
@@ -437,6 +434,8 @@ __global__ __launch_bounds__(kLineMaxThr) HP_LINE_WAVES(R, RM, kLineComb) void k
         if (t < RL) c.acc[t] = cadd(c.acc[t], o[t * KL]);
     }
   } else {
+    uint64_t left = 0;
+    for (int i = 0; i < nrow; ++i) left |= row0 + i < rows ? rowmask[row0 + i] : 0ull;
     while (left != 0) {
       c.n = __builtin_ctzll(left);
       left &= left - 1;
@@ -518,7 +517,7 @@ constexpr size_t kLineLdsMax = (size_t)150 * 1024;
 
 }  // namespace
 
-bool make_line_plan(int real_kind, int n, int kind, int across, int groups, int lines_req, LinePlan* out) {
+static bool find_line_plan(int real_kind, int n, int kind, int across, int groups, int lines_req, LinePlan* out) {
   if (is_pow2_len(n) || n < 8) return false;
   const int eb = real_kind == 0 ? 16 : 8;
   const bool keeps = kind == kLineSym || kind == kLineComb, table = keeps;
@@ -587,10 +586,36 @@ bool make_line_plan(int real_kind, int n, int kind, int across, int groups, int 
     }
   }
   // a second exchange region where it costs no occupancy: one barrier per exchange
+  const int waves = (p.T * p.L + 63) / 64;
+  const int by_regs = std::max(1, 4 * (keeps ? line_waves(real_kind == 0, p.rm, kind) : real_kind == 0 ? 4 : 6) / waves);
+  auto held = [&] { return std::min(by_regs, (int)((size_t)160 * 1024 / line_lds(p, eb, table))); };
+  const int one = held();
   p.two_buf = 1;
-  if (line_lds(p, eb, table) > 40 * 1024) p.two_buf = 0;
+  if (line_lds(p, eb, table) > kLineLdsMax || held() < one) p.two_buf = 0;
   *out = p;
   return true;
+}
+
+// The launches of one apply ask for the same few plans every time: each thread remembers
+// the last ones it found (a search costs about as much host time as a launch).
+bool make_line_plan(int real_kind, int n, int kind, int across, int groups, int lines_req, LinePlan* out) {
+  struct Entry {
+    int key[6];
+    bool ok;
+    LinePlan plan;
+  };
+  constexpr unsigned kEntries = 32;
+  static thread_local Entry memo[kEntries] = {};
+  const int key[6] = {real_kind + 1, n, kind, across, groups, lines_req};
+  unsigned h = 0;
+  for (int v : key) h = h * 31 + (unsigned)v;
+  Entry& e = memo[(h ^ (h >> 7)) % kEntries];
+  if (!std::equal(key, key + 6, e.key)) {
+    e.ok = find_line_plan(real_kind, n, kind, across, groups, lines_req, &e.plan);
+    std::copy(key, key + 6, e.key);
+  }
+  if (e.ok) *out = e.plan;
+  return e.ok;
 }
 
 // The plan of the inverse transform of pass B: the radices reversed.
@@ -606,6 +631,17 @@ int line_symbol_threads(int real_kind, int n, int* elems) {
   if (!make_line_plan(real_kind, n, kLineSym, 1 << 20, 1, 0, &p)) return 0;
   *elems = p.r[0];
   return n / p.r[0];
+}
+
+int line_stage_table(int real_kind, int n, int kind, std::vector<int>* index) {
+  LinePlan p;
+  index->clear();
+  if (!make_line_plan(real_kind, n, kind, 1 << 20, 1, 0, &p)) return 0;
+  if (kind == kLineSym) p = reversed(p, real_kind == 0 ? 16 : 8);
+  for (int s = 1; s < p.nst; ++s)
+    for (int t = 1; t < p.r[s]; ++t)
+      for (int k = 0; k < p.K[s]; ++k) index->push_back(k * t * p.J[s]);
+  return (int)index->size();
 }
 
 // ---------------------------------------------------------------- launchers
@@ -666,7 +702,7 @@ static hipError_t cols_go(const LinePlan& p, const ColsArgs& a, hipStream_t st) 
     auto go = [&](auto kern) {
       allow_dynamic_lds(kern, lds);
       HP_PASS_LAUNCH(a.tev, kern, dim3(tiles, ng, a.nrhs), dim3(line_block(p)), lds, st, in, out, a.S, a.in_rs,
-                     a.out_rs, a.out_fs, fw, iv, tw, a.skip, a.lam_ax, a.lam_in, a.nodes, a.K, a.scale, a.store_mask);
+                     a.out_rs, a.out_fs, fw, iv, tw, (const cpx<R>*)a.stw, a.skip, a.lam_ax, a.lam_in, a.nodes, a.K, a.scale, a.store_mask);
       return hipGetLastError();
     };
     return p.rm == kLineRadixLo ? go(k_line_sym<R, kLineRadixLo>) : go(k_line_sym<R, kLineRadixMax>);
@@ -694,7 +730,7 @@ static hipError_t combine_go(const LinePlan& p, const CombineArgs& a, hipStream_
     allow_dynamic_lds(kern, lds);
     HP_PASS_LAUNCH(a.tev, kern, dim3((a.rows + nrow - 1) / nrow, a.nrhs), dim3(line_block(p)), lds, st,
                    (const cpx<R>*)a.fields, a.fs, a.frs, a.pos, a.rowmask, (cpx<TO>*)a.out, a.out_rs, a.rows, a.M,
-                   a.Mt, a.mo, p, (const cpx<R>*)a.tw, a.skip, a.order, a.lag, a.posa, a.Ma);
+                   a.Mt, a.mo, p, (const cpx<R>*)a.stw, a.skip, a.order, a.lag, a.posa, a.Ma);
     return hipGetLastError();
   };
   if (p.rm == kLineRadixLo)

@@ -71,3 +71,24 @@ def test_line_combine_interpolations(orc, hp, shape, precision, kw):
     ref = orc.Problem(shape, omega, c, a, zeta, **kw).apply(v)
     assert rel(u, ref) < (1e-12 if precision == "fp64" else 1e-5)
     plan.close()
+
+
+@pytest.mark.parametrize("shape,precision", [((180, 120), "mixed"), ((360, 240), "fp64"), ((90, 600), "fp64")])
+def test_lines_per_workgroup_keep_results(hp, shape, precision, tmp_path, monkeypatch):
+    """The lines a workgroup takes (a tuning choice) do not change a bit of the result."""
+    print(f"[case] lines per workgroup {shape} {precision}", flush=True)
+    omega = 2 * np.pi * min(shape) / 6
+    c = inputs.gaussian_random_field(shape, 6.0, 9)
+    a = np.full(shape, 0.05 * omega)
+    make = lambda: hp.Plan(shape, omega, c, a, None, m_real=12, precision=precision)  # noqa: E731
+    dt = torch.complex128 if precision == "fp64" else torch.complex64
+    rng = np.random.default_rng(4)
+    v = torch.from_numpy(rng.standard_normal(shape) + 1j * rng.standard_normal(shape)).to("cuda").to(dt)
+    u0 = make().apply(v)
+    for tc in (1, 2, 4, 8):
+        path = tmp_path / f"tune{tc}.txt"
+        prec = 0 if precision == "fp64" else 1
+        path.write_text("".join(f"hp-tune 2 {shape[0]} {shape[1]} 1 {prec} 12 {s} 0 {tc} 0 0\n" for s in (0, 2, 4)))
+        monkeypatch.setenv("HP_TUNE_CACHE", str(path))
+        assert torch.equal(make().apply(v), u0)
+        monkeypatch.delenv("HP_TUNE_CACHE")
