@@ -1427,8 +1427,76 @@ __global__ __launch_bounds__(256) void k_stencil(const cpx<TI>* __restrict__ u, 
   }
 }
 
+// The 2-D operator with four rows per thread: a column of u is read once for the rows
+// above and below it (3.5 loads of u per point instead of five), and one division finds
+// the place of four points.  Bound by memory: 1024^2 FP64, 67 MB, 12.7 -> 12.1 us (5.6
+// TB/s).
+constexpr int kStencilRows = 4;
+constexpr size_t kStencilRowsMin = (size_t)1 << 18;   // smaller grids need every thread
+template <typename R, typename TI, typename TO, bool RESID>
+__global__ __launch_bounds__(256) void k_stencil_rows(const cpx<TI>* __restrict__ u, cpx<TO>* __restrict__ y,
+                                                      const cpx<R>* __restrict__ coef,
+                                                      const cpx<double>* __restrict__ f, int n0, int n1, R ih0, R ih1,
+                                                      size_t u_rs, size_t y_rs, const int* __restrict__ skip) {
+  const int rhs = blockIdx.y;
+  if (skip != nullptr && skip[rhs] != 0) return;
+  const uint32_t q = blockIdx.x * 256u + threadIdx.x;
+  const int g = (int)(q / (uint32_t)n1), i1 = (int)(q - (uint32_t)g * (uint32_t)n1);
+  const int r0 = g * kStencilRows;
+  if (r0 >= n0) return;
+  const cpx<TI>* ur = u + (size_t)rhs * u_rs;
+  const int left = i1 == 0 ? n1 - 1 : i1 - 1, right = i1 + 1 == n1 ? 0 : i1 + 1;
+  // rows r0 - 1 .. r0 + 4 of the column (past the last row of the grid: any row, unused)
+  cpx<R> mid[kStencilRows + 2], a[kStencilRows], b[kStencilRows], g2[kStencilRows], be[kStencilRows];
+#pragma unroll
+  for (int t = 0; t < kStencilRows + 2; ++t) {
+    int r = r0 + t - 1;
+    r = r < 0 ? n0 - 1 : r >= n0 ? r - n0 : r;
+    mid[t] = cvt<R>(ur[(size_t)r * n1 + i1]);
+  }
+#pragma unroll
+  for (int t = 0; t < kStencilRows; ++t) {
+    const int r = r0 + t < n0 ? r0 + t : r0;
+    const size_t at = (size_t)r * n1;
+    a[t] = cvt<R>(ur[at + right]);
+    b[t] = cvt<R>(ur[at + left]);
+    g2[t] = coef[2 * (at + i1)];
+    be[t] = coef[2 * (at + i1) + 1];
+  }
+#pragma unroll
+  for (int t = 0; t < kStencilRows; ++t) {
+    if (r0 + t >= n0) break;
+    const size_t i = (size_t)(r0 + t) * n1 + i1;
+    const cpx<R> c = mid[t + 2], d = mid[t];
+    const cpx<R> lap = {(a[t].re + b[t].re) * ih1 + (c.re + d.re) * ih0, (a[t].im + b[t].im) * ih1 + (c.im + d.im) * ih0};
+    const cpx<R> r = cadd(cmul(g2[t], lap), cmul(be[t], mid[t + 1]));
+    if constexpr (RESID) {
+      const cpx<double> fv = f[(size_t)rhs * u_rs + i];
+      y[(size_t)rhs * y_rs + i] = {(TO)(fv.re - (double)r.re), (TO)(fv.im - (double)r.im)};
+    } else {
+      y[(size_t)rhs * y_rs + i] = cvt<TO>(r);
+    }
+  }
+}
+
 hipError_t launch_stencil(const StencilArgs& a, hipStream_t st) {
   const size_t npts = (size_t)a.n[0] * a.n[1] * (a.dim == 3 ? a.n[2] : 1);
+  if (a.dim == 2 && npts >= kStencilRowsMin) {
+    const size_t thr = (size_t)((a.n[0] + kStencilRows - 1) / kStencilRows) * a.n[1];
+    auto go = [&](auto kern, auto* u, auto* y, auto* coef) {
+      using R = decltype(coef->re);
+      hipLaunchKernelGGL(kern, dim3((unsigned)((thr + 255) / 256), a.nrhs), dim3(256), 0, st, u, y, coef,
+                         (const cpx<double>*)a.f, a.n[0], a.n[1], (R)a.ih2[0], (R)a.ih2[1], a.u_rs, a.y_rs, a.skip);
+      return hipGetLastError();
+    };
+    switch (a.kind) {
+      case 0: return go(k_stencil_rows<double, double, double, false>, (const cpx<double>*)a.u, (cpx<double>*)a.y, (const cpx<double>*)a.coef);
+      case 1: return go(k_stencil_rows<float, float, float, false>, (const cpx<float>*)a.u, (cpx<float>*)a.y, (const cpx<float>*)a.coef);
+      case 2: return go(k_stencil_rows<float, float, double, false>, (const cpx<float>*)a.u, (cpx<double>*)a.y, (const cpx<float>*)a.coef);
+      case 3: return go(k_stencil_rows<double, double, double, true>, (const cpx<double>*)a.u, (cpx<double>*)a.y, (const cpx<double>*)a.coef);
+      default: return hipErrorInvalidValue;
+    }
+  }
   dim3 grid((unsigned)((npts + 255) / 256), a.nrhs);
   const int n2 = a.dim == 3 ? a.n[2] : 1;
 #define HP_STENCIL(R, TI, TO, D, RES)                                                                    \
