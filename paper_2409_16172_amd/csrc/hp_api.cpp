@@ -1491,8 +1491,12 @@ struct Session {
 
   // After kFinished: per right-hand side results (blocking copy of the states).
   hp_status collect(hp_solve_info* info) {
+    // only the scalars at the end of each state (the Hessenberg arrays before them are
+    // 130 KB per right-hand side)
+    constexpr size_t tail = offsetof(hp::KState, fnorm), len = sizeof(hp::KState) - tail;
     std::vector<hp::KState> hs(nrhs);
-    HP_TRY(hipMemcpyAsync(hs.data(), W->state.p, (size_t)nrhs * sizeof(hp::KState), hipMemcpyDeviceToHost, st));
+    HP_TRY(hipMemcpy2DAsync((char*)hs.data() + tail, sizeof(hp::KState), (const char*)W->state.p + tail, sizeof(hp::KState),
+                            len, (size_t)nrhs, hipMemcpyDeviceToHost, st));
     HP_TRY(hipStreamSynchronize(st));
     hp_status ret = HP_OK;
     for (int r = 0; r < nrhs; ++r) {

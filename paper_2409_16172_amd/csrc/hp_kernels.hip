@@ -1827,10 +1827,10 @@ constexpr int kHPrefetch = ((kMaxRestart - 1) * (kMaxRestart + 1) + kFinThreads 
 __device__ __forceinline__ void arnoldi_finalize(KState& S, const cpx<double>* part, int rhs, int j, int restart,
                                                  int* skip_step, int* host_stop, int nb) {
   __shared__ cpx<double> sums[kPartSlots];
-  __shared__ cpx<double> zz[kMaxRestart + 1], hp[kMaxRestart + 1], raw[kMaxRestart + 2];
+  __shared__ cpx<double> zz[kMaxRestart + 1], pp[kMaxRestart + 1], hn[kMaxRestart + 1];
+  __shared__ cpx<double> hp[kMaxRestart + 1], raw[kMaxRestart + 2], sh_t0;
   __shared__ cpx<double> hsh[kHPacked];
   __shared__ GivensLds L;
-  __shared__ double sh_sigma;
   __shared__ int sh_break;
   // Every load of the state this step reads (Givens rotations, g, the provisional
   // column, the finished Hessenberg columns but the last) is issued together with
@@ -1863,18 +1863,41 @@ __device__ __forceinline__ void arnoldi_finalize(KState& S, const cpx<double>* p
   const cpx<double>* a = sums;
   const cpx<double>* bv = sums + j;
   const int lane = threadIdx.x & 63;
-  if (threadIdx.x < 64) {
-    // v_j = (u_j - V a) / sigma; column j-1 = (hprov_{j-1} + a, sigma)
-    const double aa = wave_sum(lane < j ? cabs2(a[lane]) : 0.0);
-    const double s2 = sums[2 * j].re - aa;
-    const double sigma = s2 > 0.0 ? sqrt(s2) : 0.0;
-    const int brk = !(sigma > 0.0);
-    if (lane == 0) {
-      sh_sigma = sigma;
-      sh_break = brk;
+  // z = Hraw[0..j][0..j-1] a, the expansion of A V a in v_0..v_j, sixteen lanes per row k,
+  // each over every sixteenth term, summed across the sixteen in a fixed order.  Column
+  // j-1 is the one committed below, (hprov_{j-1} + a, sigma); its last entry, the only
+  // term of row j, is added where sigma is known.
+  {
+    static_assert(kFinThreads >= 16 * (kMaxRestart + 1) - 16, "one 16-lane group per row of z");
+    const int k = threadIdx.x >> 4, q = threadIdx.x & 15;
+    cpx<double> acc = {0.0, 0.0};
+    if (k < j) {
+      for (int i = (k > 0 ? k - 1 : 0) + q; i < j; i += 16)
+        acc = cadd(acc, cmul(i < j - 1 ? hsh[hpacked(i) + k] : cadd(hp[k], a[k]), a[i]));
     }
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1) {
+      acc.re += __shfl_xor(acc.re, off, 16);
+      acc.im += __shfl_xor(acc.im, off, 16);
+    }
+    if (k < j && q == 0) zz[k] = acc;
+  }
+  lds_barrier();
+  // Two wavefronts go on side by side.  Both form sigma, v_j = (u_j - V a) / sigma.
+  // Wavefront 0 commits Hessenberg column j-1: the serial chain of its rotations, the
+  // residual and the stopping test.  Wavefront 1 meanwhile forms the provisional column j
+  // and takes it through the rotations already known, 0..j-2 (one chain after the other
+  // made the kernel 15.2 us at j = 28, 13.2 side by side).
+  const bool first = threadIdx.x < 64, second = threadIdx.x >= 64 && threadIdx.x < 128;
+  const cpx<double> al = lane < j ? a[lane] : cpx<double>{0.0, 0.0};
+  const double aa = wave_sum(cabs2(al));
+  const double s2 = sums[2 * j].re - aa;
+  const double sigma = s2 > 0.0 ? sqrt(s2) : 0.0, isg = 1.0 / sigma;
+  if (first) {
+    const int brk = !(sigma > 0.0);
+    if (lane == 0) sh_break = brk;
     if (j >= 1) {
-      if (lane < j) raw[lane] = cadd(hp[lane], a[lane]);
+      if (lane < j) raw[lane] = cadd(hp[lane], al);
       if (lane == 0) raw[j] = {sigma, 0.0};
       wave_lds_sync();
       double est = 0.0;
@@ -1888,59 +1911,59 @@ __device__ __forceinline__ void arnoldi_finalize(KState& S, const cpx<double>* p
         sh_break = 1;
       }
     }
-  }
-  lds_barrier();
-  if (sh_break) return;
-  // z = Hraw[0..j][0..j-1] a, the expansion of A V a in v_0..v_j (column j-1 is
-  // the one committed above, still in raw).  Sixteen lanes per row k, each over
-  // every sixteenth term, then summed across the sixteen in a fixed order.
-  {
-    static_assert(kFinThreads >= 16 * (kMaxRestart + 1) - 16, "one 16-lane group per row of z");
-    const int k = threadIdx.x >> 4, q = threadIdx.x & 15;
-    cpx<double> acc = {0.0, 0.0};
-    if (k <= j) {
-      for (int i = (k > 0 ? k - 1 : 0) + q; i < j; i += 16)
-        acc = cadd(acc, cmul(i < j - 1 ? hsh[hpacked(i) + k] : raw[k], a[i]));
+  } else if (second) {
+    // p_j = v_j^H w, then hprov_j = [V, v_j]^H A v_j = (p - z) / sigma
+    const cpx<double> bl = lane < j ? bv[lane] : cpx<double>{0.0, 0.0};
+    const cpx<double> ab = {wave_sum(al.re * bl.re + al.im * bl.im), wave_sum(al.re * bl.im - al.im * bl.re)};
+    const cpx<double> p = lane < j ? bl : cscale(csub(sums[2 * j + 1], ab), isg);
+    const cpx<double> z = lane < j ? zz[lane] : j >= 1 ? cscale(a[j - 1], sigma) : cpx<double>{0.0, 0.0};
+    if (lane <= j) {
+      zz[lane] = z;
+      pp[lane] = p;
+      hn[lane] = cscale(csub(p, z), isg);
     }
+    wave_lds_sync();
+    // residual estimate with the provisional column: rotations 0..j-2 (operands of four
+    // loaded at once, as in commit_column)
+    cpx<double> t0 = hn[0];
+    for (int i0 = 0; i0 < j - 1; i0 += 4) {
+      cpx<double> xx[4], cc[4], ss[4];
 #pragma unroll
-    for (int off = 8; off >= 1; off >>= 1) {
-      acc.re += __shfl_xor(acc.re, off, 16);
-      acc.im += __shfl_xor(acc.im, off, 16);
+      for (int u = 0; u < 4; ++u) {
+        const int i = i0 + u < j - 1 ? i0 + u : j - 2;
+        xx[u] = hn[i + 1];
+        cc[u] = L.cs[i];
+        ss[u] = L.sn[i];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (i0 + u >= j - 1) break;
+        const cpx<double> x1 = xx[u], c = cc[u], s = ss[u];
+        t0 = {-(s.re * t0.re - s.im * t0.im) + (c.re * x1.re - c.im * x1.im),
+              -(s.re * t0.im + s.im * t0.re) + (c.re * x1.im + c.im * x1.re)};
+      }
     }
-    if (k <= j && q == 0) zz[k] = acc;
-  }
-  const double sigma = sh_sigma, isg = 1.0 / sigma;
-  if (threadIdx.x < 64) {
-    // p_j = v_j^H w
-    cpx<double> t = {0.0, 0.0};
-    if (lane < j) t = {a[lane].re * bv[lane].re + a[lane].im * bv[lane].im, a[lane].re * bv[lane].im - a[lane].im * bv[lane].re};
-    const cpx<double> ab = {wave_sum(t.re), wave_sum(t.im)};
-    if (lane == 0) raw[j] = cscale(csub(sums[2 * j + 1], ab), isg);
+    if (lane == 0) sh_t0 = t0;
   }
   lds_barrier();
-  // hprov_j = [V, v_j]^H A v_j = (p - z) / sigma (parallel over k)
-  for (int k = threadIdx.x; k <= j; k += blockDim.x) {
-    const cpx<double> pk = k < j ? bv[k] : raw[j];
-    hp[k] = cscale(csub(pk, zz[k]), isg);
-  }
-  lds_barrier();
+  if (sh_break || !(first || second)) return;
   // update coefficients: u_{j+1} = w/sigma - V cv - cu u_j, y = z/sigma + hprov_j
-  const cpx<double> cu = cscale(cadd(cscale(zz[j], isg), hp[j]), isg);
-  for (int k = threadIdx.x; k <= j; k += blockDim.x) {
-    S.hprov[k] = hp[k];
-    if (k < j) {
-      const cpx<double> yk = cadd(cscale(zz[k], isg), hp[k]);
-      S.cv[k] = csub(yk, cmul(cu, a[k]));
-      S.av[k] = a[k];
+  const cpx<double> cu = cscale(cadd(cscale(zz[j], isg), hn[j]), isg);
+  if (second) {
+    if (lane <= j) {
+      S.hprov[lane] = hn[lane];
+      if (lane < j) {
+        S.cv[lane] = csub(cadd(cscale(zz[lane], isg), hn[lane]), cmul(cu, al));
+        S.av[lane] = al;
+      }
     }
+    return;
   }
-  if (threadIdx.x >= 64) return;
   double zp = 0.0, z2 = 0.0, h2 = 0.0;
   if (lane <= j) {
-    const cpx<double> pk = lane < j ? bv[lane] : raw[j];
-    zp = zz[lane].re * pk.re + zz[lane].im * pk.im;
+    zp = zz[lane].re * pp[lane].re + zz[lane].im * pp[lane].im;
     z2 = cabs2(zz[lane]);
-    h2 = cabs2(hp[lane]);
+    h2 = cabs2(hn[lane]);
   }
   zp = wave_sum(zp);
   z2 = wave_sum(z2);
@@ -1953,25 +1976,12 @@ __device__ __forceinline__ void arnoldi_finalize(KState& S, const cpx<double>* p
   const double av2 = (sums[2 * j + 2].re - 2.0 * zp + z2) * isg * isg;   // ||A v_j||^2
   const double r2 = av2 - h2;
   const double rho = r2 > 0.0 ? sqrt(r2) : 0.0;
-  // residual estimate with the provisional column j (operands of four rotations
-  // loaded at once, as in commit_column)
-  cpx<double> t0 = hp[0];
-  for (int i0 = 0; i0 < j; i0 += 4) {
-    cpx<double> xx[4], cc[4], ss[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int i = i0 + u < j ? i0 + u : j - 1;
-      xx[u] = hp[i + 1];
-      cc[u] = L.cs[i];
-      ss[u] = L.sn[i];
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (i0 + u >= j) break;
-      const cpx<double> x1 = xx[u], c = cc[u], s = ss[u];
-      t0 = {-(s.re * t0.re - s.im * t0.im) + (c.re * x1.re - c.im * x1.im),
-            -(s.re * t0.im + s.im * t0.re) + (c.re * x1.im + c.im * x1.re)};
-    }
+  // the estimate's last rotation, j-1, just formed
+  cpx<double> t0 = sh_t0;
+  if (j >= 1) {
+    const cpx<double> x1 = hn[j], c = L.cs[j - 1], s = L.sn[j - 1];
+    t0 = {-(s.re * t0.re - s.im * t0.im) + (c.re * x1.re - c.im * x1.im),
+          -(s.re * t0.im + s.im * t0.re) + (c.re * x1.im + c.im * x1.re)};
   }
   const double tt = sqrt(cabs2(t0));
   const double den = sqrt(tt * tt + rho * rho);
@@ -1980,7 +1990,7 @@ __device__ __forceinline__ void arnoldi_finalize(KState& S, const cpx<double>* p
   if (est <= target || breakdown || j + 1 >= restart) {
     // end the cycle with the provisional column j (its second projection would
     // change it by the loss of orthogonality only)
-    if (lane <= j) raw[lane] = hp[lane];
+    if (lane <= j) raw[lane] = hn[lane];
     if (lane == 0) raw[j + 1] = {rho, 0.0};
     wave_lds_sync();
     if (lane == 0) commit_column(S, L, j, raw, iters);
@@ -2479,15 +2489,20 @@ __global__ __launch_bounds__(256) void k_backsolve(KState* state, const int* don
   }
   for (int t = threadIdx.x; t < k; t += blockDim.x) y[t] = S.g[t];
   __syncthreads();
-  if (threadIdx.x != 0) return;
+  // one wavefront, by columns: y_i is final, then lane l takes R_li y_i off y_l for all
+  // l < i at once (a step is one LDS latency; one thread by rows took 22 us at k = 30)
+  if (threadIdx.x >= 64) return;
+  const int l = threadIdx.x;
+  cpx<double> yl = l < k ? y[l] : cpx<double>{0.0, 0.0};
   for (int i = k - 1; i >= 0; --i) {
-    cpx<double> s = y[i];
-    for (int l = i + 1; l < k; ++l) s = csub(s, cmul(R[i * kMaxRestart + l], y[l]));
-    const cpx<double> d = R[i * kMaxRestart + i];
+    const cpx<double> d = R[i * kMaxRestart + i], r = l < i ? R[l * kMaxRestart + i] : cpx<double>{0.0, 0.0};
     const double dd = cabs2(d);
-    y[i] = {(s.re * d.re + s.im * d.im) / dd, (s.im * d.re - s.re * d.im) / dd};
+    const cpx<double> q = {(yl.re * d.re + yl.im * d.im) / dd, (yl.im * d.re - yl.re * d.im) / dd};
+    const cpx<double> yi = {__shfl(q.re, i, 64), __shfl(q.im, i, 64)};
+    if (l == i) yl = yi;
+    else yl = csub(yl, cmul(r, yi));
   }
-  for (int i = 0; i < k; ++i) S.y[i] = y[i];
+  if (l < k) S.y[l] = yl;
 }
 
 // out = sum_{i<k} y_i v_i
