@@ -164,9 +164,16 @@ def _host(a, shape):
 
 
 def _stream(stream):
+    """The hipStream_t of `stream` (None: the caller's current stream) as an integer.  The
+    raw handle of the current stream is asked for directly: building a Stream object for
+    it took 2.5 of the 6 us a call spent outside the library."""
     import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch.cuda.current_device())
 
 
 def _order_on(stream, *tensors):
@@ -294,11 +301,14 @@ class Plan:
         """u = Q_M v for one field or a batch [nrhs, *shape]."""
         import torch
         nr = self._fields(v, self.field_dtype, "v")
-        u = torch.empty_like(v) if out is None else out
-        self._same_count(nr, u, self.field_dtype, "out")
+        if out is None:
+            u = torch.empty_like(v)
+        else:
+            u = out
+            self._same_count(nr, u, self.field_dtype, "out")
         _order_on(stream, v, u)
-        _check(load_library().hp_apply_precond(self._h, C.c_void_p(v.data_ptr()), C.c_void_p(u.data_ptr()),
-                                               nr, _stream(stream)), "hp_apply_precond")
+        _check(load_library().hp_apply_precond(self._h, v.data_ptr(), u.data_ptr(), nr, _stream(stream)),
+               "hp_apply_precond")
         return u
 
     def apply_static(self, v, out=None, stream=None):
@@ -322,11 +332,13 @@ class Plan:
         """y = P_N u for one field or a batch."""
         import torch
         nr = self._fields(u, self.field_dtype, "u")
-        y = torch.empty_like(u) if out is None else out
-        self._same_count(nr, y, self.field_dtype, "out")
+        if out is None:
+            y = torch.empty_like(u)
+        else:
+            y = out
+            self._same_count(nr, y, self.field_dtype, "out")
         _order_on(stream, u, y)
-        _check(load_library().hp_matvec(self._h, C.c_void_p(u.data_ptr()), C.c_void_p(y.data_ptr()), nr,
-                                        _stream(stream)), "hp_matvec")
+        _check(load_library().hp_matvec(self._h, u.data_ptr(), y.data_ptr(), nr, _stream(stream)), "hp_matvec")
         return y
 
     def solve(self, f, x=None, *, restart=30, max_cycles=200, rtol=1e-8, stream=None, raise_on_fail=False,
