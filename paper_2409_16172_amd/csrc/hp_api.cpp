@@ -71,7 +71,6 @@ struct hp_plan_s {
   // device data
   DevBuf nodes, pos, grpmask, rowmask, slabneed, storemask, coef64, coef32, lam_ax, lam_in, tw64[3], tw32[3];
   int order = 1;   // real-axis interpolation degree in effect
-  DevBuf stw_b, stw_c;   // stage tables of passes B and C (mixed-radix lines)
   DevBuf lagtab;   // Lagrange table of CombineArgs::lag (order >= 2)
   hp::PassTune tune[5];   // run-time choices of passes A, A', B, M, C (hp_plan_autotune)
   int tune_gen = 0;        // bumped when they change (captured step graphs become stale)
@@ -100,9 +99,11 @@ struct hp_plan_s {
   int real_kind() const { return prec == HP_FP64 ? 0 : 1; }
   size_t fsize() const { return prec == HP_FP64 ? 16 : 8; }
   const void* tw(int axis) const { return prec == HP_FP64 ? tw64[axis].p : tw32[axis].p; }
+  // the stage table behind the n[axis] roots (mixed-radix lines of passes B and C)
+  const void* stw(int axis) const { return (const char*)tw(axis) + (size_t)n[axis] * fsize(); }
   void release_all() {
     for (DevBuf* b : {&nodes, &pos, &grpmask, &rowmask, &slabneed, &storemask, &coef64, &coef32, &lam_ax, &lam_in, &t,
-                      &fields, &lagtab, &posa, &stw_b, &stw_c})
+                      &fields, &lagtab, &posa})
       b->release();
     for (int i = 0; i < 3; ++i) { tw64[i].release(); tw32[i].release(); }
     release_solver_ws();
@@ -627,25 +628,17 @@ hp_status hp_plan_create(hp_plan* out, const hp_grid* grid, double omega, const 
       w[m] = {std::cos(ang), -std::sin(ang)};
       wf[m] = {(float)w[m].re, (float)w[m].im};
     }
-    if (P->prec == HP_FP64) {
-      if ((e = upload(P->tw64[d], w)) != hipSuccess) return failc(from_hip(e));
-    } else {
-      if ((e = upload(P->tw32[d], wf)) != hipSuccess) return failc(from_hip(e));
-    }
-    // the same roots in the order the register lines of passes B (axis 0) and C (last axis) read them
-    for (int kind : {hp::kLineSym, hp::kLineComb}) {
-      std::vector<int> at;
-      if (d != (kind == hp::kLineSym ? 0 : P->dim - 1) || hp::line_stage_table(P->real_kind(), n, kind, &at) == 0) continue;
-      DevBuf& buf = kind == hp::kLineSym ? P->stw_b : P->stw_c;
-      std::vector<cpx<double>> sw(at.size());
-      std::vector<cpx<float>> swf(at.size());
-      for (size_t q = 0; q < at.size(); ++q) {
-        sw[q] = w[at[q]];
-        swf[q] = wf[at[q]];
+    // then the same roots in the order the register lines of passes B (axis 0) and C (last
+    // axis) read them, in the same buffer (an upload of its own took 0.3 ms of plan set-up)
+    std::vector<int> at;
+    const int kind = d == 0 ? hp::kLineSym : hp::kLineComb;
+    if ((d == 0 || d == P->dim - 1) && hp::line_stage_table(P->real_kind(), n, kind, &at) > 0)
+      for (int m : at) {
+        w.push_back(w[m]);
+        wf.push_back(wf[m]);
       }
-      e = P->prec == HP_FP64 ? upload(buf, sw) : upload(buf, swf);
-      if (e != hipSuccess) return failc(from_hip(e));
-    }
+    e = P->prec == HP_FP64 ? upload(P->tw64[d], w) : upload(P->tw32[d], wf);
+    if (e != hipSuccess) return failc(from_hip(e));
   }
   const size_t fb = (size_t)P->max_nrhs * np * P->fsize();
   if ((e = P->t.alloc(fb)) != hipSuccess) return failc(from_hip(e));
@@ -816,7 +809,7 @@ hipError_t apply_passes(hp_plan_s* P, const void* v, int in_kind, size_t in_rs, 
   hp::ColsArgs b{};
   b.real_kind = rk; b.n = P->n[0]; b.dir = -1; b.mode = 1;
   b.in = wt; b.out = wf; b.S = (int)(np / P->n[0]); b.outer = 1; b.nfields = 1; b.nrhs = nrhs;
-  b.in_rs = np; b.out_rs = np * P->K; b.in_fs = np; b.out_fs = np; b.tw = P->tw(0); b.stw = P->stw_b.p; b.skip = skip;
+  b.in_rs = np; b.out_rs = np * P->K; b.in_fs = np; b.out_fs = np; b.tw = P->tw(0); b.stw = P->stw(0); b.skip = skip;
   b.lam_ax = (const double*)P->lam_ax.p; b.lam_in = (const double*)P->lam_in.p;
   b.nodes = (const hp::NodeConst*)P->nodes.p; b.K = P->K; b.scale = 1.0 / (double)np;
   b.store_mask = (const uint16_t*)P->storemask.p;
@@ -842,7 +835,7 @@ hipError_t apply_passes(hp_plan_s* P, const void* v, int in_kind, size_t in_rs, 
   c.real_kind = rk; c.out_kind = out_kind; c.accumulate = acc ? 1 : 0; c.n = nl;
   c.fields = wf; c.fs = np; c.frs = np * P->K; c.pos = (const double*)P->pos.p;
   c.grpmask = (const uint64_t*)P->grpmask.p; c.rowmask = (const uint64_t*)P->rowmask.p; c.out = u; c.out_rs = out_rs; c.rows = rows; c.K = P->K;
-  c.M = P->M; c.Mt = P->Mt; c.mo = P->mo; c.nrhs = nrhs; c.tw = P->tw(P->dim - 1); c.stw = P->stw_c.p; c.skip = skip;
+  c.M = P->M; c.Mt = P->Mt; c.mo = P->mo; c.nrhs = nrhs; c.tw = P->tw(P->dim - 1); c.stw = P->stw(P->dim - 1); c.skip = skip;
   c.order = P->order; c.lag = (const double*)P->lagtab.p;
   c.posa = (const double*)P->posa.p; c.Ma = P->Ma;
   c.tune = P->tune[4];
