@@ -1530,10 +1530,39 @@ hipError_t launch_stencil(const StencilArgs& a, hipStream_t st) {
 // sums of the kRedBlocks blocks of a right-hand side are added in a fixed order.
 constexpr int kChunk = 16;
 
+// v of lane (lane ^ X), X <= 8, every lane of the wavefront active: lane moves inside a row
+// of 16 by data-parallel operands (a quad permutation, a shift each way for half the banks,
+// a rotation), a few cycles where a shuffle through LDS takes its latency.
+template <int X>
+__device__ __forceinline__ int lane_xor(int v) {
+  static_assert(X == 1 || X == 2 || X == 4 || X == 8, "inside a row of 16 lanes");
+  if (X == 1) return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, true);    // quad_perm 1 0 3 2
+  if (X == 2) return __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, true);    // quad_perm 2 3 0 1
+  if (X == 8) return __builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, true);   // row_ror:8
+  const int up = __builtin_amdgcn_update_dpp(0, v, 0x104, 0xF, 0x5, false);      // row_shl:4, lanes 0-3 and 8-11
+  return __builtin_amdgcn_update_dpp(up, v, 0x114, 0xF, 0xA, false);             // row_shr:4, the others
+}
+
+// v + (v of lane ^ X).  Lanes 16 and 32 apart are swapped between two copies of v.
+template <int X>
+__device__ __forceinline__ double add_xor(double v) {
+  const int lo = __double2loint(v), hi = __double2hiint(v);
+  if constexpr (X == 32 || X == 16) {
+    const auto a = X == 32 ? __builtin_amdgcn_permlane32_swap(lo, lo, false, false)
+                           : __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto b = X == 32 ? __builtin_amdgcn_permlane32_swap(hi, hi, false, false)
+                           : __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    return __hiloint2double((int)b[0], (int)a[0]) + __hiloint2double((int)b[1], (int)a[1]);
+  } else {
+    return v + __hiloint2double(lane_xor<X>(hi), lane_xor<X>(lo));
+  }
+}
+
+// Sum over the wavefront (all lanes active), the same in every lane: a butterfly over lanes
+// 32, 16, .. 1 apart.  The finishing kernel is a chain of such sums, the sweep ends in them:
+// with shuffles a 256^2 FP64 solve of two cycles took 2860 us, with these 2715.
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
+  return add_xor<1>(add_xor<2>(add_xor<4>(add_xor<8>(add_xor<16>(add_xor<32>(v))))));
 }
 
 // Reduce `cnt` complex values per thread over the block and write them to part.
@@ -1853,7 +1882,10 @@ __device__ __forceinline__ void arnoldi_finalize(KState& S, const cpx<double>* p
   }
   const double target = S.target;
   int iters = S.iters;
+  // so is the flag of a finished cycle: asked first, it would put its own latency before theirs
+  const int over = skip_step[rhs];
   reduce_slots(part, rhs, 2 * j + 3, sums, nb);   // ends with a barrier
+  if (over) return;
   if (t < kMaxRestart) { L.cs[t] = rc; L.sn[t] = rs; }
   if (t <= kMaxRestart) { L.g[t] = rg; hp[t] = rh; }
 #pragma unroll
@@ -1875,11 +1907,8 @@ __device__ __forceinline__ void arnoldi_finalize(KState& S, const cpx<double>* p
       for (int i = (k > 0 ? k - 1 : 0) + q; i < j; i += 16)
         acc = cadd(acc, cmul(i < j - 1 ? hsh[hpacked(i) + k] : cadd(hp[k], a[k]), a[i]));
     }
-#pragma unroll
-    for (int off = 8; off >= 1; off >>= 1) {
-      acc.re += __shfl_xor(acc.re, off, 16);
-      acc.im += __shfl_xor(acc.im, off, 16);
-    }
+    acc.re = add_xor<1>(add_xor<2>(add_xor<4>(add_xor<8>(acc.re))));
+    acc.im = add_xor<1>(add_xor<2>(add_xor<4>(add_xor<8>(acc.im))));
     if (k < j && q == 0) zz[k] = acc;
   }
   lds_barrier();
@@ -1887,7 +1916,7 @@ __device__ __forceinline__ void arnoldi_finalize(KState& S, const cpx<double>* p
   // Wavefront 0 commits Hessenberg column j-1: the serial chain of its rotations, the
   // residual and the stopping test.  Wavefront 1 meanwhile forms the provisional column j
   // and takes it through the rotations already known, 0..j-2 (one chain after the other
-  // made the kernel 15.2 us at j = 28, 13.2 side by side).
+  // made the kernel 15.2 us at j = 28, 13.2 side by side; 9.4 with the sums of add_xor).
   const bool first = threadIdx.x < 64, second = threadIdx.x >= 64 && threadIdx.x < 128;
   const cpx<double> al = lane < j ? a[lane] : cpx<double>{0.0, 0.0};
   const double aa = wave_sum(cabs2(al));
@@ -2198,7 +2227,6 @@ __global__ __launch_bounds__(kFinThreads) void k_arnoldi_fin(const cpx<double>* 
                                                       KState* state, int j, int restart, int* __restrict__ host_stop,
                                                       int nb) {
   const int rhs = blockIdx.x;
-  if (skip_step[rhs]) return;
   arnoldi_finalize(state[rhs], part, rhs, j, restart, skip_step, host_stop, nb);
 }
 
@@ -2474,6 +2502,11 @@ __device__ __forceinline__ void arnoldi_update_body(cpx<double>* __restrict__ V,
 }
 
 
+// v of lane i (the same i in every lane).
+__device__ __forceinline__ double lane_value(double v, int i) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), i), __builtin_amdgcn_readlane(__double2loint(v), i));
+}
+
 // y = R^{-1} g over the k finished columns (upper triangular back substitution),
 // with R and g staged in LDS.
 __global__ __launch_bounds__(256) void k_backsolve(KState* state, const int* done) {
@@ -2498,7 +2531,7 @@ __global__ __launch_bounds__(256) void k_backsolve(KState* state, const int* don
     const cpx<double> d = R[i * kMaxRestart + i], r = l < i ? R[l * kMaxRestart + i] : cpx<double>{0.0, 0.0};
     const double dd = cabs2(d);
     const cpx<double> q = {(yl.re * d.re + yl.im * d.im) / dd, (yl.im * d.re - yl.re * d.im) / dd};
-    const cpx<double> yi = {__shfl(q.re, i, 64), __shfl(q.im, i, 64)};
+    const cpx<double> yi = {lane_value(q.re, i), lane_value(q.im, i)};
     if (l == i) yl = yi;
     else yl = csub(yl, cmul(r, yi));
   }
@@ -3056,7 +3089,6 @@ struct GFinDesc {
 
 __global__ __launch_bounds__(kFinThreads) void k_group_fin(const GroupArgs<GFinDesc> a) {
   const GFinDesc& d = a.m[blockIdx.x];
-  if (d.skip[0] != 0) return;
   arnoldi_finalize(d.state[0], d.part, 0, d.j, d.restart, d.skip, d.host_stop, d.nb);
 }
 
