@@ -9,7 +9,7 @@
  *   - Grids: d = 2 or 3 dimensions, n[j] points per axis, each a power of two in
  *     [8, 2048] (FP64 plans) or [8, 4096] (mixed plans), or an even product of
  *     2, 3 and 5 in [8, 4800] (such as the N = 180 * 2^k and 2400 of Section 5.1;
- *     these lines are transformed in LDS by mixed-radix stages), fewer than 2^32
+ *     these lines take mixed-radix stages, in registers or LDS), fewer than 2^32
  *     points in all; side len[j]; spacing h_j = len[j]/n[j]; periodic boundary
  *     conditions (Section 5).
  *   - Fields: row-major with the last axis contiguous, complex interleaved
@@ -365,11 +365,12 @@ hp_status hp_plan_time_pass(hp_plan p, int slot);
 hp_status hp_plan_pass_times(hp_plan p, double* ms, int cap, int* count);
 
 /* Autotuner of the transform passes: for each pass in turn, times the plan's apply
- * (one right-hand side) under every valid run-time choice — threads per line, lines
- * per workgroup and radix schedule of the mixed-radix passes (N = 2^a 3^b 5^c),
- * node groups per column tile of the power-of-two symbol pass, node splits of the
- * power-of-two combine (lines of at most 1024 points) — and keeps the fastest (by
- * at least 2 %); the plan then uses it for every apply, solve step and session.
+ * (one right-hand side) under every valid run-time choice — lines per workgroup of the
+ * mixed-radix passes (N = 2^a 3^b 5^c; threads per line and radix schedule too where a
+ * line is held in LDS rather than registers), node groups per column tile of the
+ * power-of-two symbol pass, node splits of the power-of-two combine (lines of at most
+ * 1024 points) — and keeps the fastest (by at least 2 %); the plan then uses it for
+ * every apply, solve step and session.
  * Only the radix schedule and the node splits change results (rounding).
  * If the environment variable HP_TUNE_CACHE names a file the choices are appended
  * to it, and hp_plan_create reads it for plans of the same grid, precision and K.

@@ -1484,12 +1484,12 @@ struct Session {
 
   // After kFinished: per right-hand side results (blocking copy of the states).
   hp_status collect(hp_solve_info* info) {
-    // only the scalars at the end of each state (the Hessenberg arrays before them are
-    // 130 KB per right-hand side)
-    constexpr size_t tail = offsetof(hp::KState, fnorm), len = sizeof(hp::KState) - tail;
+    // from the scalars at the end of the first state on (the Hessenberg arrays before them are
+    // 130 KB).  A plain copy: a strided one of the scalars alone left them zero under a profiler.
+    constexpr size_t tail = offsetof(hp::KState, fnorm);
     std::vector<hp::KState> hs(nrhs);
-    HP_TRY(hipMemcpy2DAsync((char*)hs.data() + tail, sizeof(hp::KState), (const char*)W->state.p + tail, sizeof(hp::KState),
-                            len, (size_t)nrhs, hipMemcpyDeviceToHost, st));
+    HP_TRY(hipMemcpyAsync((char*)hs.data() + tail, (const char*)W->state.p + tail, sizeof(hp::KState) * nrhs - tail,
+                          hipMemcpyDeviceToHost, st));
     HP_TRY(hipStreamSynchronize(st));
     hp_status ret = HP_OK;
     for (int r = 0; r < nrhs; ++r) {

@@ -60,9 +60,10 @@ __host__ __device__ constexpr int sweep_blocks(size_t npts) {
   return npts <= ((size_t)1 << 16) ? kRedBlocks / 2 : kRedBlocks;
 }
 
-// Mixed-radix lines (N = 2^a 3^b 5^c, not a power of two): stage radices in
-// order, threads per line and (column passes) lines per workgroup.  A thread
-// holds at most E elements of a line: kGenRowE in pass A, gen_e<R>() in the
+// Mixed-radix lines held in LDS: those the register lines below do not take (lengths
+// without four radices of at most 16, FP64 column passes over powers of two above 2048)
+// and radix schedules 1 to 3 of a tuning file.  Stage radices in order, threads per line
+// and (column passes) lines per workgroup.  A thread holds at most E elements of a line: kGenRowE in pass A, gen_e<R>() in the
 // column passes and in pass C.
 constexpr int kGenRowE = 16;
 // column passes and pass C: FP64 lines with 10 elements per thread and at most 512
@@ -105,7 +106,7 @@ constexpr int kGenOrders = 4;
 // Every mixed-radix kernel can take lines of length n.
 bool gen_length_ok(int n);
 inline bool is_pow2_len(int n) { return n > 0 && (n & (n - 1)) == 0; }
-// Column passes (strided axes) take the LDS-resident mixed-radix kernels for
+// Column passes (strided axes) take the mixed-radix kernels (of either kind) for
 // lengths that are not powers of two, and for FP64 power-of-two lengths above
 // 2048, whose register-tile column kernel would not fit in LDS.
 bool cols_use_gen(int real_kind, int n);
@@ -150,8 +151,9 @@ int line_stage_table(int real_kind, int n, int kind, std::vector<int>* index);
 // j + threads * t) and the elements each stores; 0 if these kernels do not take n.
 int line_symbol_threads(int real_kind, int n, int* elems);
 
-// Run-time choices of a transform pass (0 = the built-in choice): threads per line,
-// lines per workgroup (column passes) and radix schedule of the mixed-radix passes,
+// Run-time choices of a transform pass (0 = the built-in choice): threads per line and
+// radix schedule of mixed-radix lines held in LDS (register lines have one of each),
+// lines per workgroup of either kind,
 // node groups per column tile of the power-of-two symbol pass, node splits (1 or 4)
 // of the power-of-two pass C.  Only the radix schedule and the node splits change
 // results (rounding: the order of the node sum).
