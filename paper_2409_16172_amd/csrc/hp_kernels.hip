@@ -189,6 +189,17 @@ __device__ __forceinline__ void cols_body(
   const int rhs = (MODE == 0) ? z / nfields : z;
   const int fld = (MODE == 0) ? z % nfields : 0;
   if (skip != nullptr && skip[rhs] != 0) return;
+  // Workgroups are dispatched round-robin over the 8 XCDs (each with its own L2).  Give
+  // the workgroups of one XCD consecutive column tiles so that tiles sharing cache lines
+  // meet in the same L2.  In the symbol pass tile counts that eight does not divide run on
+  // over the node groups (in dispatch order: 1024 x 1000 FP64 108 us, now 78, mixed 70 and
+  // 56; 2048 x 2000 mixed 518 and 281, 2048 x 1944 FP64 1203 and 530).  The plain passes'
+  // wider tiles share no lines and keep it.
+  int tile = bx;
+#if HP_XCD_REMAP
+  if ((gx & 7) == 0) tile = (bx & 7) * (gx >> 3) + (bx >> 3);
+  else if (MODE == 1) xcd_tile(bx, by, gx, gy, &tile, &by);
+#endif
   // plain passes over node fields: slabs whose points never use this node are skipped
   if (MODE == 0 && slab_need != nullptr && slab_need[(size_t)fld * gy + by] == 0) return;
   // With the lane exchange threads j and j ^ 64 of a column sit at lanes l and l ^ 32
@@ -197,13 +208,6 @@ __device__ __forceinline__ void cols_body(
   const int g = SWP ? (lane & 1) : (int)threadIdx.x % C::TC;
   const int j = SWP ? (((lane >> 1) & 15) | ((int)(threadIdx.x >> 6) << 4) | ((lane >> 5) << 6))
                     : (int)threadIdx.x / C::TC;
-  // Workgroups are dispatched round-robin over the 8 XCDs (each with its own
-  // L2).  Give the workgroups of one XCD consecutive column tiles so that tiles
-  // sharing cache lines meet in the same L2.
-  int tile = bx;
-#if HP_XCD_REMAP
-  if ((gx & 7) == 0) tile = (bx & 7) * (gx >> 3) + (bx >> 3);
-#endif
   const int c = tile * C::TC + g;
   const bool act = c < S;
   // MODE 0: by is the outer (slab) index.  MODE 1 (outer = 1): by is the node
