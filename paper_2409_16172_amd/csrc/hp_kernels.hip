@@ -1248,10 +1248,16 @@ struct CombineL {
         // 19.4, 512^2 FP32 25.0 -> 18.2; eight splits gave 7.9, 27.6 and 19.0.  The
         // choice depends on the plan only, so that a batch sums in the order a single
         // field does.
+        // FP32 lines of 256 points take them on grids of any size: four wavefronts on one
+        // row's nodes read longer runs at once than one on each of four rows (256^3, K = 19:
+        // 463 -> 334 us, K = 6: 267 -> 228; 128 x 128 x 256: 138 -> 95 and 70 -> 58).  At 512
+        // points that holds for many nodes only (K = 19 253 -> 226, K = 6 130 -> 152), at
+        // 128 and 1024 for none (128^3 37 -> 39, 128 x 64 x 1024 281 -> 324).
         const int groups = (int)grid.x;
+        const bool always = sizeof(R) == 4 && N == 256 && a.K >= 3;
         const int ns = a.tune.ng > 0 ? a.tune.ng
-                       : (groups <= 256 && a.K >= 3) || (groups <= 1024 && a.K >= 8) ? kCombineSplits
-                                                                                      : 1;
+                       : always || (groups <= 256 && a.K >= 3) || (groups <= 1024 && a.K >= 8) ? kCombineSplits
+                                                                                                : 1;
         if (ns == kCombineSplits) {
           combine_launch<R, TO, N, ACC, kCombineSplits>(a, grid, st);
           return hipGetLastError();
