@@ -691,14 +691,6 @@ hp_status hp_plan_query(hp_plan p, hp_plan_info* info) {
 
 namespace {
 
-// u (+)= Q_M v for nrhs <= max_nrhs right-hand sides.
-// in_kind/out_kind: 0 = complex128, 1 = complex64.
-// ev (optional): 6 events recorded before pass A and after each of the five
-// pass slots (A, A', B, M, C; the 3-D-only slots are recorded even when empty).
-// reps (profiling only, with acc false): the out-of-place passes A, B and C are
-// launched reps times back to back between their events; they read and write
-// disjoint buffers, so a repeat recomputes the same result.  The in-place
-// middle-axis passes of 3-D grids are launched once.
 // Flags of the solver's step and cycle events.  They only tell the host how far
 // the device has got; what it then reads (the stop/done flags) is in coherent
 // pinned memory that the kernels store to directly, so the events need no
@@ -755,6 +747,17 @@ hipError_t timer_events(hp_plan_s* P, hipStream_t st, const hipEvent_t** tev) {
   return hipSuccess;
 }
 
+// Launch of pass `slot`, with the timer's events when that pass is timed.
+template <typename F>
+hipError_t timed_pass(hp_plan_s* P, int slot, bool can_time, hipStream_t st, F&& launch) {
+  const hipEvent_t* tev = nullptr;
+  if (P->timer_slot == slot && can_time) {
+    const hipError_t e = timer_events(P, st, &tev);
+    if (e != hipSuccess) return e;
+  }
+  return launch(tev);
+}
+
 // Where an apply keeps its intermediate spectrum t and its K node fields: the
 // plan's workspace, or (hp_apply_precond_static) the static device array.
 struct ApplyWs {
@@ -762,50 +765,44 @@ struct ApplyWs {
   void* fields;
 };
 
-// The passes of one apply over nrhs fields, with the spectrum in wt and the node fields
-// in wf.  from_b: pass A's output is already in wt (the fused update of the previous
-// Arnoldi step wrote it); the apply starts at pass B.  can_time: the pass timer may
-// create events.
-hipError_t apply_passes(hp_plan_s* P, const void* v, int in_kind, size_t in_rs, void* u, int out_kind,
-                        size_t out_rs, bool acc, int nrhs, const int* skip, hipStream_t st, hipEvent_t* ev, int reps,
-                        void* const wt, void* const wf, bool can_time, bool from_b) {
+// Passes A and A' of an apply over nrhs fields: their spectra along the last axes, into wt.
+// can_time: the pass timer may create events (here and in apply_back).
+hipError_t apply_front(hp_plan_s* P, const void* v, int in_kind, size_t in_rs, int nrhs, const int* skip,
+                       hipStream_t st, hipEvent_t* ev, int reps, void* const wt, bool can_time) {
   const int rk = P->real_kind();
   const size_t np = P->npts;
   hipError_t e;
   const int nl = P->n[P->dim - 1];
   const int rows = (int)(np / nl);
-  // the middle-axis slots (2 and 4) only exist in 3-D
-  auto mark = [&](int i) {
-    return (ev && (P->dim == 3 || (i != 2 && i != 4))) ? hipEventRecord(ev[i], st) : hipSuccess;
-  };
-  // launch of pass `slot`, with the timer's events when that pass is timed
-  auto timed = [&](int slot, auto&& launch) -> hipError_t {
-    const hipEvent_t* tev = nullptr;
-    if (P->timer_slot == slot && can_time) {   // the static-workspace path creates no events
-      hipError_t e2 = timer_events(P, st, &tev);
-      if (e2 != hipSuccess) return e2;
-    }
-    return launch(tev);
-  };
-  if ((e = mark(0)) != hipSuccess) return e;
-  for (int r = 0; r < (from_b ? 0 : reps); ++r) {
-    e = timed(0, [&](const hipEvent_t* tev) {
+  for (int r = 0; r < reps; ++r) {
+    e = timed_pass(P, 0, can_time, st, [&](const hipEvent_t* tev) {
       return hp::launch_rows_fwd(rk, in_kind, nl, v, wt, rows, in_rs, np, nrhs, P->tw(P->dim - 1), skip,
                                  P->tune[0], st, tev);
     });
     if (e != hipSuccess) return e;
   }
-  if ((e = mark(1)) != hipSuccess) return e;
+  if (ev && (e = hipEventRecord(ev[1], st)) != hipSuccess) return e;
   if (P->dim == 3) {   // forward along the middle axis, in place
     hp::ColsArgs m{};
     m.real_kind = rk; m.n = P->n[1]; m.dir = -1; m.mode = 0;
     m.in = wt; m.out = wt; m.S = P->n[2]; m.outer = P->n[0]; m.nfields = 1; m.nrhs = nrhs;
     m.in_rs = np; m.out_rs = np; m.in_fs = np; m.out_fs = np; m.tw = P->tw(1); m.skip = skip;
     m.tune = P->tune[1];
-    if ((e = timed(1, [&](const hipEvent_t* tev) { m.tev = tev; return hp::launch_cols(m, st); })) != hipSuccess)
+    if ((e = timed_pass(P, 1, can_time, st, [&](const hipEvent_t* tev) { m.tev = tev; return hp::launch_cols(m, st); })) != hipSuccess)
       return e;
+    if (ev && (e = hipEventRecord(ev[2], st)) != hipSuccess) return e;
   }
-  if ((e = mark(2)) != hipSuccess) return e;
+  return hipSuccess;
+}
+
+// Passes B, M and C over nrhs fields whose spectra are in wt, with their node fields in wf.
+hipError_t apply_back(hp_plan_s* P, void* u, int out_kind, size_t out_rs, bool acc, int nrhs, const int* skip,
+                      hipStream_t st, hipEvent_t* ev, int reps, void* const wt, void* const wf, bool can_time) {
+  const int rk = P->real_kind();
+  const size_t np = P->npts;
+  hipError_t e;
+  const int nl = P->n[P->dim - 1];
+  const int rows = (int)(np / nl);
   hp::ColsArgs b{};
   b.real_kind = rk; b.n = P->n[0]; b.dir = -1; b.mode = 1;
   b.in = wt; b.out = wf; b.S = (int)(np / P->n[0]); b.outer = 1; b.nfields = 1; b.nrhs = nrhs;
@@ -817,9 +814,9 @@ hipError_t apply_passes(hp_plan_s* P, const void* v, int in_kind, size_t in_rs, 
   b.store_need = (const uint8_t*)P->slabneed.p;
   b.tune = P->tune[2];
   for (int r = 0; r < reps; ++r)
-    if ((e = timed(2, [&](const hipEvent_t* tev) { b.tev = tev; return hp::launch_cols(b, st); })) != hipSuccess)
+    if ((e = timed_pass(P, 2, can_time, st, [&](const hipEvent_t* tev) { b.tev = tev; return hp::launch_cols(b, st); })) != hipSuccess)
       return e;
-  if ((e = mark(3)) != hipSuccess) return e;
+  if (ev && (e = hipEventRecord(ev[0], st)) != hipSuccess) return e;
   if (P->dim == 3) {   // inverse along the middle axis for the K fields, in place
     hp::ColsArgs m{};
     m.real_kind = rk; m.n = P->n[1]; m.dir = +1; m.mode = 0;
@@ -827,10 +824,10 @@ hipError_t apply_passes(hp_plan_s* P, const void* v, int in_kind, size_t in_rs, 
     m.in_rs = np * P->K; m.out_rs = np * P->K; m.in_fs = np; m.out_fs = np; m.tw = P->tw(1); m.skip = skip;
     m.slab_need = (const uint8_t*)P->slabneed.p;
     m.tune = P->tune[3];
-    if ((e = timed(3, [&](const hipEvent_t* tev) { m.tev = tev; return hp::launch_cols(m, st); })) != hipSuccess)
+    if ((e = timed_pass(P, 3, can_time, st, [&](const hipEvent_t* tev) { m.tev = tev; return hp::launch_cols(m, st); })) != hipSuccess)
       return e;
+    if (ev && (e = hipEventRecord(ev[1], st)) != hipSuccess) return e;
   }
-  if ((e = mark(4)) != hipSuccess) return e;
   hp::CombineArgs c{};
   c.real_kind = rk; c.out_kind = out_kind; c.accumulate = acc ? 1 : 0; c.n = nl;
   c.fields = wf; c.fs = np; c.frs = np * P->K; c.pos = (const double*)P->pos.p;
@@ -840,16 +837,16 @@ hipError_t apply_passes(hp_plan_s* P, const void* v, int in_kind, size_t in_rs, 
   c.posa = (const double*)P->posa.p; c.Ma = P->Ma;
   c.tune = P->tune[4];
   for (int r = 0; r < (acc ? 1 : reps); ++r)
-    if ((e = timed(4, [&](const hipEvent_t* tev) { c.tev = tev; return hp::launch_combine(c, st); })) != hipSuccess)
+    if ((e = timed_pass(P, 4, can_time, st, [&](const hipEvent_t* tev) { c.tev = tev; return hp::launch_combine(c, st); })) != hipSuccess)
       return e;
-  return mark(5);
+  return ev ? hipEventRecord(ev[2], st) : hipSuccess;
 }
 
-// Fields of a batch one run of the passes takes.  Where a field fills the chip by itself
-// and its used node rows fit the 256 MiB Infinity Cache (and a batch's do not), the batch
-// runs in parts that reuse the same node-field memory, so that passes M and C find in the
-// cache what pass B wrote (128^3 x 4 mixed, K = 19: 802 -> 695 us).  The
-// results do not depend on it.
+// Fields of a batch that passes B, M and C take at once.  Where a field fills the chip by
+// itself and its used node rows fit the 256 MiB Infinity Cache (and a batch's do not), they
+// run the batch in parts that reuse the same node-field memory, so that passes M and C find
+// in the cache what pass B wrote (128^3 x 4 mixed, K = 19: 802 -> 695 us).  The results do
+// not depend on it.
 int batch_part(const hp_plan_s* P, int nrhs) {
   constexpr double kCache = 256.0 * (1 << 20);
   const double one = P->slabs_used * (double)(P->npts / P->n[0]) * (double)P->fsize();
@@ -857,19 +854,32 @@ int batch_part(const hp_plan_s* P, int nrhs) {
   return std::max(1, (int)(kCache / one));
 }
 
-// u = Q_M v (or u += Q_M v) for nrhs fields in_rs and out_rs elements apart.
+// u = Q_M v (or u += Q_M v) for nrhs <= max_nrhs fields in_rs and out_rs elements apart.
+// in_kind/out_kind: 0 = complex128, 1 = complex64.  Every field's passes A and A' come
+// before the first write to u, so u may overlap v in any way.
+// ev, reps (profiling only, with acc false): events recorded before pass A, after it and
+// (3-D) after A', after B, (3-D) after M, and after C, over the whole batch; the
+// out-of-place passes A, B and C are launched reps times back to back between their
+// events; they read and write disjoint buffers, so a repeat recomputes the same result.
+// The in-place middle-axis passes of 3-D grids are launched once.
+// from_b: pass A's output is already in the spectrum buffer (the fused update of the
+// previous Arnoldi step wrote it); the apply starts at pass B.
 hipError_t run_apply(hp_plan_s* P, const void* v, int in_kind, size_t in_rs, void* u, int out_kind,
                      size_t out_rs, bool acc, int nrhs, const int* skip, hipStream_t st,
                      hipEvent_t* ev = nullptr, int reps = 1, const ApplyWs* ws = nullptr, bool from_b = false) {
   if (!ws && !from_b) P->t_owner = nullptr;
   char* const wt = (char*)(ws ? ws->t : P->t.p);
   void* const wf = ws ? ws->fields : P->fields.p;
+  const bool can_time = ws == nullptr;   // the static-workspace path creates no events
+  hipError_t e;
+  if (ev && (e = hipEventRecord(ev[0], st)) != hipSuccess) return e;
+  if (!from_b && (e = apply_front(P, v, in_kind, in_rs, nrhs, skip, st, ev, reps, wt, can_time)) != hipSuccess)
+    return e;
   const int part = ev ? nrhs : batch_part(P, nrhs);
-  const size_t fb = P->npts * P->fsize(), ib = in_rs * (in_kind == 0 ? 16 : 8), ob = out_rs * (out_kind == 0 ? 16 : 8);
+  const size_t fb = P->npts * P->fsize(), ob = out_rs * (out_kind == 0 ? 16 : 8);
   for (int r0 = 0; r0 < nrhs; r0 += part) {
-    const hipError_t e = apply_passes(P, (const char*)v + ib * r0, in_kind, in_rs, (char*)u + ob * r0, out_kind, out_rs,
-                                      acc, std::min(part, nrhs - r0), skip ? skip + r0 : nullptr, st, ev, reps,
-                                      wt + fb * r0, wf, ws == nullptr, from_b);
+    e = apply_back(P, (char*)u + ob * r0, out_kind, out_rs, acc, std::min(part, nrhs - r0), skip ? skip + r0 : nullptr,
+                   st, ev ? ev + 3 : nullptr, reps, wt + fb * r0, wf, can_time);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -883,29 +893,28 @@ hipError_t run_apply(hp_plan_s* P, const void* v, int in_kind, size_t in_rs, voi
 // once).
 hipError_t time_passes(hp_plan_s* p, const void* v, void* u, int nrhs, int reps, double* ms, hipStream_t st) {
   const int kind = p->prec == HP_FP64 ? 0 : 1;
-  hipEvent_t ev[6];
-  for (int i = 0; i < 6; ++i) {
-    hipError_t e = hipEventCreate(&ev[i]);
-    if (e != hipSuccess) {
-      for (int k = 0; k < i; ++k) (void)hipEventDestroy(ev[k]);
-      return e;
-    }
+  std::vector<hipEvent_t> ev;
+  hipError_t err = hipSuccess;
+  while (err == hipSuccess && ev.size() < 6) {
+    hipEvent_t x;
+    if ((err = hipEventCreate(&x)) == hipSuccess) ev.push_back(x);
   }
   double acc[5] = {0, 0, 0, 0, 0};
-  hipError_t err = run_apply(p, v, kind, p->npts, u, kind, p->npts, false, nrhs, nullptr, st);
-  if (err == hipSuccess) err = run_apply(p, v, kind, p->npts, u, kind, p->npts, false, nrhs, nullptr, st, ev, reps);
-  if (err == hipSuccess) err = hipEventSynchronize(ev[5]);
-  const int slots3[5][2] = {{0, 1}, {1, 2}, {2, 3}, {3, 4}, {4, 5}};
-  const int slots2[5][2] = {{0, 1}, {-1, -1}, {1, 3}, {-1, -1}, {3, 5}};
-  const int count[5] = {reps, 1, reps, 1, reps};
-  for (int i = 0; i < 5 && err == hipSuccess; ++i) {
-    const int a = p->dim == 3 ? slots3[i][0] : slots2[i][0], b = p->dim == 3 ? slots3[i][1] : slots2[i][1];
-    if (a < 0) continue;
+  if (err == hipSuccess) err = run_apply(p, v, kind, p->npts, u, kind, p->npts, false, nrhs, nullptr, st);
+  if (err == hipSuccess) err = run_apply(p, v, kind, p->npts, u, kind, p->npts, false, nrhs, nullptr, st, ev.data(), reps);
+  if (err == hipSuccess) err = hipEventSynchronize(ev.back());
+  auto add = [&](int slot, int from, int to, int count) {
     float t = 0;
-    err = hipEventElapsedTime(&t, ev[a], ev[b]);
-    acc[i] = (double)t / count[i];
-  }
-  for (int i = 0; i < 6; ++i) (void)hipEventDestroy(ev[i]);
+    if (err == hipSuccess) err = hipEventElapsedTime(&t, ev[from], ev[to]);
+    acc[slot] += (double)t / count;
+  };
+  const bool d3 = p->dim == 3;
+  add(0, 0, 1, reps);
+  if (d3) add(1, 1, 2, 1);
+  add(2, d3 ? 2 : 1, 3, reps);
+  if (d3) add(3, 3, 4, 1);
+  add(4, d3 ? 4 : 3, 5, reps);
+  for (hipEvent_t x : ev) (void)hipEventDestroy(x);
   for (int i = 0; i < 5; ++i) ms[i] = acc[i];
   return err;
 }
