@@ -1478,6 +1478,8 @@ struct Session {
     m.j = j;
     m.restart = o.restart;
     m.ng_b = P->tune[2].ng;
+    const int nl = P->n[P->dim - 1];
+    m.splits = hp::combine_splits(P->real_kind(), nl, (int)(P->npts / nl), P->K, P->tune[4]);
     if (!hp::group_member_ok(m)) return false;
     *g = m;
     return true;

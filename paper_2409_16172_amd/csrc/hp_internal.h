@@ -235,6 +235,8 @@ constexpr int kLagTable = kMaxNodes * 5;
 hipError_t launch_combine(const CombineArgs& a, hipStream_t st);
 hipError_t launch_line_combine(const LinePlan& p, const CombineArgs& a, hipStream_t st);
 int combine_group_rows(int real_kind, int n);        // rows per workgroup of pass C
+// Node splits of pass C over `rows` power-of-two lines (1 for lines that cannot split).
+int combine_splits(int real_kind, int n, int rows, int K, const PassTune& tune);
 int symbol_pass_line_threads(int real_kind, int n);  // threads per line T of pass B
 // threads per line of the built-in mixed-radix symbol-pass plan (0 if n has none) and
 // the elements each thread holds
@@ -328,6 +330,7 @@ struct GroupMember {
   int* host_stop;
   int j, restart;
   int ng_b;                   // node groups of the symbol pass (0: the single-plan choice)
+  int splits;                 // node splits of pass C (combine_splits of the member's plan)
 };
 // Whether a member's grid and options are ones the grouped kernels take (the grouped
 // step then gives bitwise the result of the member's own step).

@@ -1002,7 +1002,26 @@ static bool make_col_plan(int n, int S, int mode, GenPlan* gp, const PassTune& t
   return true;
 }
 
-bool combine_splits_ok(int real_kind, int n);   // pass C of this length can split its nodes
+// pass C of this length can split its nodes
+static bool combine_splits_ok(int real_kind, int n) { return is_pow2_len(n) && n <= (real_kind == 0 ? 64 * HP_E64 : 64 * HP_E32); }
+
+// Node splits while the row groups' wavefronts leave the chip idle, or as tuned (the
+// tuner's node-group field): 64^2 FP64 13.2 -> 8.4 us, 512^2 FP64 29.5 -> 19.4, 512^2 FP32
+// 25.0 -> 18.2; eight splits gave 7.9, 27.6 and 19.0.  The choice depends on the plan only,
+// so that a batch sums in the order a single field does, and a step in a grouped launch in
+// the order of the member's own step.
+// FP32 lines of 256 points take them on grids of any size: four wavefronts on one row's
+// nodes read longer runs at once than one on each of four rows (256^3, K = 19: 463 -> 334
+// us, K = 6: 267 -> 228; 128 x 128 x 256: 138 -> 95 and 70 -> 58).  At 512 points that holds
+// for many nodes only (K = 19 253 -> 226, K = 6 130 -> 152), at 128 and 1024 for none (128^3
+// 37 -> 39, 128 x 64 x 1024 281 -> 324).
+int combine_splits(int real_kind, int n, int rows, int K, const PassTune& tune) {
+  if (!combine_splits_ok(real_kind, n)) return 1;
+  if (tune.ng > 0) return tune.ng == kCombineSplits ? kCombineSplits : 1;
+  const int g = combine_group_rows(real_kind, n), groups = (rows + g - 1) / g;
+  const bool always = real_kind == 1 && n == 256 && K >= 3;
+  return always || (groups <= 256 && K >= 3) || (groups <= 1024 && K >= 8) ? kCombineSplits : 1;
+}
 
 bool cols_use_gen(int real_kind, int n) { return !is_pow2_len(n) || (real_kind == 0 && n > 2048); }
 
@@ -1243,22 +1262,7 @@ struct CombineL {
       using C = CombCfg<R, N>;
       dim3 grid((a.rows + C::G - 1) / C::G, a.nrhs);
       if constexpr (combine_splits_fit<R, N>()) {
-        // node splits while the row groups' wavefronts leave the chip idle, or as tuned
-        // (the tuner's node-group field): 64^2 FP64 13.2 -> 8.4 us, 512^2 FP64 29.5 ->
-        // 19.4, 512^2 FP32 25.0 -> 18.2; eight splits gave 7.9, 27.6 and 19.0.  The
-        // choice depends on the plan only, so that a batch sums in the order a single
-        // field does.
-        // FP32 lines of 256 points take them on grids of any size: four wavefronts on one
-        // row's nodes read longer runs at once than one on each of four rows (256^3, K = 19:
-        // 463 -> 334 us, K = 6: 267 -> 228; 128 x 128 x 256: 138 -> 95 and 70 -> 58).  At 512
-        // points that holds for many nodes only (K = 19 253 -> 226, K = 6 130 -> 152), at
-        // 128 and 1024 for none (128^3 37 -> 39, 128 x 64 x 1024 281 -> 324).
-        const int groups = (int)grid.x;
-        const bool always = sizeof(R) == 4 && N == 256 && a.K >= 3;
-        const int ns = a.tune.ng > 0 ? a.tune.ng
-                       : always || (groups <= 256 && a.K >= 3) || (groups <= 1024 && a.K >= 8) ? kCombineSplits
-                                                                                                : 1;
-        if (ns == kCombineSplits) {
+        if (combine_splits(sizeof(R) == 8 ? 0 : 1, N, a.rows, a.K, a.tune) == kCombineSplits) {
           combine_launch<R, TO, N, ACC, kCombineSplits>(a, grid, st);
           return hipGetLastError();
         }
@@ -1289,7 +1293,6 @@ struct CombineL {
   };
 };
 
-bool combine_splits_ok(int real_kind, int n) { return is_pow2_len(n) && n <= (real_kind == 0 ? 64 * HP_E64 : 64 * HP_E32); }
 
 hipError_t launch_combine(const CombineArgs& a, hipStream_t st) {
   if (!is_pow2_len(a.n)) {
@@ -2328,11 +2331,11 @@ __global__ __launch_bounds__(256) void k_arnoldi_update(cpx<double>* __restrict_
 // oracle's does not (36^2 plain GMRES(64): 112 steps with either, 107 in exact symmetry).
 constexpr size_t kUpdSmallMin = 4096, kUpdSmallMax = (size_t)1 << 18;
 constexpr int kUpdSmallChunk = 8;
-__global__ __launch_bounds__(256) void k_arnoldi_update_small(cpx<double>* __restrict__ V, size_t npts, size_t vrs,
-                                                              const KState* __restrict__ state,
-                                                              const int* __restrict__ skip_step, int j) {
+__host__ __device__ constexpr bool update_small(size_t npts) { return npts >= kUpdSmallMin && npts < kUpdSmallMax; }
+__device__ __forceinline__ void arnoldi_update_small_body(cpx<double>* __restrict__ V, size_t npts, size_t vrs,
+                                                          const KState* __restrict__ state,
+                                                          const int* __restrict__ skip_step, int j, int rhs, int bx) {
   __shared__ cpx<double> ca[kMaxRestart + kUpdSmallChunk], cc[kMaxRestart + kUpdSmallChunk];
-  const int rhs = blockIdx.y;
   const KState& S = state[rhs];
   if (skip_step[rhs] && S.stop_at != j) return;
   for (int i = threadIdx.x; i < kMaxRestart + kUpdSmallChunk; i += blockDim.x) {
@@ -2340,7 +2343,7 @@ __global__ __launch_bounds__(256) void k_arnoldi_update_small(cpx<double>* __res
     cc[i] = i < j ? S.cv[i] : cpx<double>{0.0, 0.0};
   }
   __syncthreads();
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+  const size_t i = (size_t)bx * 256 + threadIdx.x;
   if (i >= npts) return;
   cpx<double>* Vr = V + (size_t)rhs * vrs;
   cpx<double>* U = Vr + (size_t)j * npts;
@@ -2367,6 +2370,12 @@ __global__ __launch_bounds__(256) void k_arnoldi_update_small(cpx<double>* __res
   const cpx<double> cuu = cmul(cu, u);
   U[i] = cscale(csub(u, sa), isg);
   W[i] = {w.re * isg - sc.re - cuu.re, w.im * isg - sc.im - cuu.im};
+}
+
+__global__ __launch_bounds__(256) void k_arnoldi_update_small(cpx<double>* __restrict__ V, size_t npts, size_t vrs,
+                                                              const KState* __restrict__ state,
+                                                              const int* __restrict__ skip_step, int j) {
+  arnoldi_update_small_body(V, npts, vrs, state, skip_step, j, blockIdx.y, blockIdx.x);
 }
 
 // The update for FP64 2-D grids whose rows (512 to 2048 points) run the register
@@ -2869,7 +2878,7 @@ hipError_t launch_arnoldi_update_rows(const KrylovArgs& a, int j, void* t, int n
 }
 
 hipError_t launch_arnoldi_update(const KrylovArgs& a, int j, hipStream_t st) {
-  if (a.npts >= kUpdSmallMin && a.npts < kUpdSmallMax) {
+  if (update_small(a.npts)) {
     hipLaunchKernelGGL(k_arnoldi_update_small, dim3((unsigned)((a.npts + 255) / 256), a.nrhs), dim3(256), 0, st, a.V,
                        a.npts, a.vrs, a.state, a.skip_step, j);
     return hipGetLastError();
@@ -2909,8 +2918,11 @@ hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t st) {
 // One launch per pass over several sessions of different grids and media (FP32
 // preconditioner, right preconditioning, one right-hand side each): the member
 // tables travel in the kernel arguments, each workgroup finds its member from the
-// block offsets and runs the same body as the member's own kernel, with the same
-// workgroup shape, so the results are bitwise those of the member's own step.
+// block offsets and runs the body that the member's own step would: pass C with the
+// plan's node splits (combine_splits; a launch for the members with and one for those
+// without), the update of the member's size (update_small), the sweep over the same
+// blocks and in the same order of points (sweep_blocks).  The results are bitwise those
+// of the member's own step, alone or as one of a batch.
 // Line lengths: 256-1024 on 2-D grids, 128-512 on 3-D grids.
 template <typename D>
 struct GroupArgs {
@@ -2946,7 +2958,9 @@ static_assert(RowCfg<float, 128>::THREADS == 256 && RowCfg<float, 1024>::THREADS
 static_assert(ColsCfg<float, 128, 1>::THREADS == 256 && ColsCfg<float, 1024, 1>::THREADS == 256 &&
                   ColsCfg<float, 128, 0>::THREADS == 256 && ColsCfg<float, 512, 0>::THREADS == 256,
               "grouped column pass shape");
-static_assert(CombCfg<float, 128>::THREADS == 64, "grouped combine shape");
+static_assert(CombCfg<float, 128>::THREADS == 64 && CombCfg<float, 256>::THREADS == 64 &&
+                  CombCfg<float, 512>::THREADS == 64 && CombCfg<float, 1024>::THREADS == 64,
+              "grouped combine shape");
 
 struct GRowsDesc {
   const cpx<double>* in;
@@ -3042,13 +3056,38 @@ __device__ __forceinline__ void group_combine_im(const GCombDesc& d, int bx, cpx
 #undef HP_GCOMB_WAVE
 }
 
-// one launch per interpolation mode present among the members
+// one launch per interpolation mode and number of node splits present among the members
 template <int IM>
 __global__ __launch_bounds__(64, 2) void k_group_combine(const GroupArgs<GCombDesc> a) {
   __shared__ cpx<float> lds[group_comb_lds()];
   __shared__ double slag[IM == kInterpLagrange ? kLagTable : 1];
   const GCombDesc& d = a.m[group_member_of(a)];
   group_combine_im<IM>(d, (int)blockIdx.x - d.block0, lds, slag);
+}
+
+constexpr int group_comb_split_lds() {
+  return std::max({combine_lds_elems<float, 128, kCombineSplits>(), combine_lds_elems<float, 256, kCombineSplits>(),
+                   combine_lds_elems<float, 512, kCombineSplits>(), combine_lds_elems<float, 1024, kCombineSplits>()});
+}
+template <int IM>
+__global__ __launch_bounds__(64 * kCombineSplits) __attribute__((amdgpu_waves_per_eu(2))) void k_group_combine_split(
+    const GroupArgs<GCombDesc> a) {
+  __shared__ cpx<float> lds[group_comb_split_lds()];
+  __shared__ double slag[IM == kInterpLagrange ? kLagTable : 1];
+  const GCombDesc& d = a.m[group_member_of(a)];
+  const int bx = (int)blockIdx.x - d.block0;
+#define HP_GCOMB_SPLIT(NN)                                                                                            \
+  rows_combine_body<float, float, NN, false, IM, kCombineSplits>(d.fields, d.fs, d.frs, d.pos, d.grpmask, d.rowmask, \
+                                                                 d.out, 0, d.rows, d.K, d.M, d.Mt, d.mo, d.tw, d.skip, \
+                                                                 d.ord, d.lag, d.posa, d.Ma, bx, 0, lds, slag)
+  switch (d.n) {
+    case 128: HP_GCOMB_SPLIT(128); break;
+    case 256: HP_GCOMB_SPLIT(256); break;
+    case 512: HP_GCOMB_SPLIT(512); break;
+    case 1024: HP_GCOMB_SPLIT(1024); break;
+    default: break;
+  }
+#undef HP_GCOMB_SPLIT
 }
 
 // w = P_N z with the 2-D or the 3-D stencil chosen at run time (the same per-point
@@ -3112,7 +3151,10 @@ struct GUpdDesc {
 
 __global__ __launch_bounds__(256) void k_group_update(const GroupArgs<GUpdDesc> a) {
   const GUpdDesc& d = a.m[group_member_of(a)];
-  arnoldi_update_body(d.V, d.npts, 0, d.state, d.skip, d.j, 0, (int)blockIdx.x - d.block0, d.gx);
+  if (update_small(d.npts))
+    arnoldi_update_small_body(d.V, d.npts, 0, d.state, d.skip, d.j, 0, (int)blockIdx.x - d.block0);
+  else
+    arnoldi_update_body(d.V, d.npts, 0, d.state, d.skip, d.j, 0, (int)blockIdx.x - d.block0, d.gx);
 }
 
 static bool group_line_ok(int dim, int n) {
@@ -3231,11 +3273,13 @@ hipError_t launch_group_step(const GroupMember* m, int count, hipStream_t st) {
   }
   if ((e = middle(+1)) != hipSuccess) return e;
   // pass C: inverse along the contiguous axis and the weighted sum into z
-  for (int im = kInterpLinear; im <= kInterpBilinear; ++im) {
+  for (int kind = 0; kind < 6; ++kind) {
+    const int im = kind % 3;
+    const bool split = kind >= 3;
     GroupArgs<GCombDesc> Cb{};
     int blocks = 0, c = 0;
     for (int q = 0; q < count; ++q) {
-      if (m[q].interp != im) continue;
+      if (m[q].interp != im || (m[q].splits == kCombineSplits) != split) continue;
       const int nl = m[q].n[m[q].dim - 1];
       const int rows = (int)(m[q].npts / nl);
       GCombDesc d{};
@@ -3260,14 +3304,20 @@ hipError_t launch_group_step(const GroupMember* m, int count, hipStream_t st) {
       d.n = nl;
       d.im = m[q].interp;
       d.block0 = blocks;
-      blocks += nl == 128 ? (rows + CombCfg<float, 128>::G - 1) / CombCfg<float, 128>::G : rows;
+      // the wave bodies take a row per workgroup, the others a row group
+      const int g = split || nl == 128 ? combine_group_rows(1, nl) : 1;
+      blocks += (rows + g - 1) / g;
       Cb.m[c++] = d;
     }
     Cb.count = c;
     if (c == 0) continue;
-    if (im == kInterpLagrange) hipLaunchKernelGGL(k_group_combine<kInterpLagrange>, dim3(blocks), dim3(64), 0, st, Cb);
-    else if (im == kInterpBilinear) hipLaunchKernelGGL(k_group_combine<kInterpBilinear>, dim3(blocks), dim3(64), 0, st, Cb);
-    else hipLaunchKernelGGL(k_group_combine<kInterpLinear>, dim3(blocks), dim3(64), 0, st, Cb);
+    auto go = [&](auto one, auto four) {
+      if (split) hipLaunchKernelGGL(four, dim3(blocks), dim3(64 * kCombineSplits), 0, st, Cb);
+      else hipLaunchKernelGGL(one, dim3(blocks), dim3(64), 0, st, Cb);
+    };
+    if (im == kInterpLagrange) go(k_group_combine<kInterpLagrange>, k_group_combine_split<kInterpLagrange>);
+    else if (im == kInterpBilinear) go(k_group_combine<kInterpBilinear>, k_group_combine_split<kInterpBilinear>);
+    else go(k_group_combine<kInterpLinear>, k_group_combine_split<kInterpLinear>);
   }
   // w = P_N z with the dot products of the step, then the finishing kernel and the update
   {
@@ -3284,7 +3334,7 @@ hipError_t launch_group_step(const GroupMember* m, int count, hipStream_t st) {
       dblocks += sweep_blocks(g.npts);
       F.m[q] = GFinDesc{g.part, g.skip_step, g.state, g.host_stop, g.j, g.restart, sweep_blocks(g.npts)};
       const size_t ub = (g.npts + 256 * kUpdPts - 1) / (256 * kUpdPts);
-      const int gx = (int)(ub < 1024 ? ub : 1024);
+      const int gx = (int)(update_small(g.npts) ? (g.npts + 255) / 256 : ub < 1024 ? ub : 1024);
       U.m[q] = GUpdDesc{g.V, g.state, g.skip_step, g.npts, g.j, gx, ublocks};
       ublocks += gx;
     }
