@@ -333,8 +333,11 @@ __device__ __forceinline__ void rows_combine_body(
       for (int s = 0; s < C::E; ++s) x[s] = {0, 0};
     }
   };
-  // the first node's row and the points' records in one memory latency
-  if (left != 0) load_row(__builtin_ctzll(left));
+  // linear mode: the first node's row and the points' records in one memory latency, and a
+  // node's row loaded behind the weights of the one before.  The other modes decode their
+  // records and weights at length, with no registers to hold a row meanwhile.
+  constexpr bool AHEAD = IM == kInterpLinear;
+  if (AHEAD && left != 0) load_row(__builtin_ctzll(left));
   CombPoint<R, IM, hat_weights<R>(N)> pt[C::E];
   cpx<R> acc[C::E];
 #pragma unroll
@@ -348,6 +351,7 @@ __device__ __forceinline__ void rows_combine_body(
   }
   while (left != 0) {
     const int n = __builtin_ctzll(left);
+    if constexpr (!AHEAD) load_row(n);
 #pragma unroll
     for (int q = 0; q < NS; ++q) left &= left - 1;   // 0 stays 0
     fft_e<R, N, C::E, +1, true, 1, false, SWP>(x, lg, j, tw);
@@ -357,7 +361,7 @@ __device__ __forceinline__ void rows_combine_body(
       acc[s].re += w * x[s].re;
       acc[s].im += w * x[s].im;
     }
-    if (left != 0) load_row(__builtin_ctzll(left));
+    if (AHEAD && left != 0) load_row(__builtin_ctzll(left));
   }
   if constexpr (NS > 1) {
     // the splits' partial sums meet in LDS; every thread adds some points' NS terms in
@@ -393,8 +397,12 @@ __device__ __forceinline__ void rows_combine_body(
   }
 }
 
+// Waves per SIMD the kernel is compiled for: two, or under Lagrange interpolation, whose
+// records and weights keep up to 34 registers more than two leave (FP32 4096), as many as
+// fit without spills.
+constexpr int combine_waves(int im) { return im == kInterpLagrange ? 1 : 2; }
 template <typename R, typename TO, int N, bool ACC, int IM, int NS = 1>
-__global__ __launch_bounds__((CombCfg<R, N>::THREADS * NS)) __attribute__((amdgpu_waves_per_eu(2))) void k_rows_combine(
+__global__ __launch_bounds__((CombCfg<R, N>::THREADS * NS)) __attribute__((amdgpu_waves_per_eu(combine_waves(IM)))) void k_rows_combine(
     const cpx<R>* __restrict__ fields, size_t fs, size_t frs, const double* __restrict__ pos,
     const uint64_t* __restrict__ grpmask, const uint64_t* __restrict__ rowmask, cpx<TO>* __restrict__ out,
     size_t out_rs, int rows, int K, int M, int Mt, int mo, const cpx<R>* __restrict__ tw,
