@@ -433,6 +433,11 @@ constexpr bool wave_line_fits() {
   return N >= 256 && N / 64 <= 16;
 }
 constexpr int kWaveRows = 4;   // rows (one per wavefront) per workgroup of the wave combine
+// Hat weights but at 512 points, where they take 132 registers and with them one of four
+// waves per SIMD: 1024 x 512, K = 7, four fields, 36 us with selects, 45 with hats, 39 with
+// hats held to 128 registers (which drops loads in flight: 17 us for one field, not 14).
+template <typename R>
+constexpr bool wave_hat_weights(int n) { return hat_weights<R>(n) && n != 512; }
 
 // Pass C with one row per wavefront: inverse transform of each node row the row
 // uses (its own node list, not its workgroup's) and the weighted sum; loads and
@@ -455,7 +460,7 @@ __device__ __forceinline__ void comb_wave_body(
   const int row = bx * WR + wv;
   if (row >= rows) return;   // no workgroup barrier follows
   const size_t rbase = (size_t)row * N;
-  CombPoint<R, IM, hat_weights<R>(N)> pt[E];
+  CombPoint<R, IM, wave_hat_weights<R>(N)> pt[E];
   cpx<R> acc[E];
 #pragma unroll
   for (int s = 0; s < E; ++s) {
