@@ -765,6 +765,18 @@ struct ApplyWs {
   void* fields;
 };
 
+// Fields of a batch that passes B, M and C take at once.  Where a field fills the chip by
+// itself and its used node rows fit the 256 MiB Infinity Cache (and a batch's do not), they
+// run the batch in parts that reuse the same node-field memory, so that passes M and C find
+// in the cache what pass B wrote (128^3 x 4 mixed, K = 19: 802 -> 695 us).  The results do
+// not depend on it.
+int batch_part(const hp_plan_s* P, int nrhs) {
+  constexpr double kCache = 256.0 * (1 << 20);
+  const double one = P->slabs_used * (double)(P->npts / P->n[0]) * (double)P->fsize();
+  if (P->npts < ((size_t)1 << 20) || one > kCache || one * nrhs <= kCache) return nrhs;
+  return std::max(1, (int)(kCache / one));
+}
+
 // Passes A and A' of an apply over nrhs fields: their spectra along the last axes, into wt.
 // can_time: the pass timer may create events (here and in apply_back).
 hipError_t apply_front(hp_plan_s* P, const void* v, int in_kind, size_t in_rs, int nrhs, const int* skip,
@@ -832,7 +844,7 @@ hipError_t apply_back(hp_plan_s* P, void* u, int out_kind, size_t out_rs, bool a
   c.real_kind = rk; c.out_kind = out_kind; c.accumulate = acc ? 1 : 0; c.n = nl;
   c.fields = wf; c.fs = np; c.frs = np * P->K; c.pos = (const double*)P->pos.p;
   c.grpmask = (const uint64_t*)P->grpmask.p; c.rowmask = (const uint64_t*)P->rowmask.p; c.out = u; c.out_rs = out_rs; c.rows = rows; c.K = P->K;
-  c.M = P->M; c.Mt = P->Mt; c.mo = P->mo; c.nrhs = nrhs; c.tw = P->tw(P->dim - 1); c.stw = P->stw(P->dim - 1); c.skip = skip;
+  c.M = P->M; c.Mt = P->Mt; c.mo = P->mo; c.nrhs = nrhs; c.batch = batch_part(P, P->max_nrhs); c.tw = P->tw(P->dim - 1); c.stw = P->stw(P->dim - 1); c.skip = skip;
   c.order = P->order; c.lag = (const double*)P->lagtab.p;
   c.posa = (const double*)P->posa.p; c.Ma = P->Ma;
   c.tune = P->tune[4];
@@ -840,18 +852,6 @@ hipError_t apply_back(hp_plan_s* P, void* u, int out_kind, size_t out_rs, bool a
     if ((e = timed_pass(P, 4, can_time, st, [&](const hipEvent_t* tev) { c.tev = tev; return hp::launch_combine(c, st); })) != hipSuccess)
       return e;
   return ev ? hipEventRecord(ev[2], st) : hipSuccess;
-}
-
-// Fields of a batch that passes B, M and C take at once.  Where a field fills the chip by
-// itself and its used node rows fit the 256 MiB Infinity Cache (and a batch's do not), they
-// run the batch in parts that reuse the same node-field memory, so that passes M and C find
-// in the cache what pass B wrote (128^3 x 4 mixed, K = 19: 802 -> 695 us).  The results do
-// not depend on it.
-int batch_part(const hp_plan_s* P, int nrhs) {
-  constexpr double kCache = 256.0 * (1 << 20);
-  const double one = P->slabs_used * (double)(P->npts / P->n[0]) * (double)P->fsize();
-  if (P->npts < ((size_t)1 << 20) || one > kCache || one * nrhs <= kCache) return nrhs;
-  return std::max(1, (int)(kCache / one));
 }
 
 // u = Q_M v (or u += Q_M v) for nrhs <= max_nrhs fields in_rs and out_rs elements apart.
@@ -1479,7 +1479,8 @@ struct Session {
     m.restart = o.restart;
     m.ng_b = P->tune[2].ng;
     const int nl = P->n[P->dim - 1];
-    m.splits = hp::combine_splits(P->real_kind(), nl, (int)(P->npts / nl), P->K, P->tune[4]);
+    m.splits = hp::combine_splits(P->real_kind(), nl, (int)(P->npts / nl), batch_part(P, P->max_nrhs), P->K, m.interp,
+                                  P->tune[4]);
     if (!hp::group_member_ok(m)) return false;
     *g = m;
     return true;

@@ -1018,26 +1018,41 @@ static bool make_col_plan(int n, int S, int mode, GenPlan* gp, const PassTune& t
 // pass C of this length can split its nodes
 static bool combine_splits_ok(int real_kind, int n) { return is_pow2_len(n) && n <= (real_kind == 0 ? 64 * HP_E64 : 64 * HP_E32); }
 
-// Node splits while the row groups' wavefronts leave the chip idle, or as tuned (the
-// tuner's node-group field): 64^2 FP64 13.2 -> 8.4 us, 512^2 FP64 29.5 -> 19.4, 512^2 FP32
-// 25.0 -> 18.2; eight splits gave 7.9, 27.6 and 19.0.  The choice depends on the plan only,
-// so that a batch sums in the order a single field does, and a step in a grouped launch in
-// the order of the member's own step.
-// FP32 lines of 256 points take them on grids of any size: four wavefronts on one row's
-// nodes read longer runs at once than one on each of four rows (256^3, K = 19: 463 -> 334
-// us, K = 6: 267 -> 228; 128 x 128 x 256: 138 -> 95 and 70 -> 58).  At 512 points that holds
-// for many nodes only (K = 19 253 -> 226, K = 6 130 -> 152), at 128 and 1024 for none (128^3
-// 37 -> 39, 128 x 64 x 1024 281 -> 324).
-int combine_splits(int real_kind, int n, int rows, int K, const PassTune& tune) {
+// Node splits, or as tuned (the tuner's node-group field).  The choice depends on the plan
+// only (for its largest launch), so that a batch sums in the order a
+// single field does, and a step in a grouped launch in the order of the member's own step.
+// `fill` wavefronts hold a node's rows without splits; four times as many fill the 1024
+// SIMDs from 512 on, and then the records decoded four times, the nodes of a group's other
+// rows and the two barriers tell.  Measured as applies without splits / with four, rows of
+// 64 to 1024 points, 128 to 1024 of them, one to eight right-hand sides (eight splits gave
+// nothing over four):
+//   up to 512: linear 1.03-1.15 at 512 and 1.2-1.7 at 128 (K = 5 to 19; 0.97-1.0 at K = 2),
+//     Lagrange 1.0-1.5 at 512, bilinear 1.02-2.0.  FP32 rows of 256 points, four to a
+//     wavefront there but one to a wavefront without, in the other modes: 0.85-0.99 below
+//     eleven nodes, 1.03-1.2 from there on;
+//   up to 1024: linear and FP32 bilinear 0.95-1.0 below eleven nodes, 0.98-1.1 from there
+//     on (FP32 bilinear 0.99-1.45); Lagrange 1.0-1.2 where four rows or more share a
+//     wavefront group (FP32 128, FP64 256 points and below), 0.7-1.0 elsewhere;
+//   above: FP32 linear rows of 256 points 1.18-1.29 at 2048 (four wavefronts on one row's
+//     nodes read longer runs at once than one on each of four rows: 256^3, K = 19, pass C
+//     463 -> 334 us) and of 512 from eleven nodes on 1.01-1.14; all others 0.5-1.04.
+int combine_splits(int real_kind, int n, int rows, int batch, int K, int interp, const PassTune& tune) {
   if (!combine_splits_ok(real_kind, n)) return 1;
   if (tune.ng > 0) return tune.ng == kCombineSplits ? kCombineSplits : 1;
-  const int g = combine_group_rows(real_kind, n), groups = (rows + g - 1) / g;
-  const bool always = real_kind == 1 && n == 256 && K >= 3;
-  return always || (groups <= 256 && K >= 3) || (groups <= 1024 && K >= 8) ? kCombineSplits : 1;
+  const int g = combine_group_rows(real_kind, n);
+  const long fill = (long)((rows + g - 1) / g) * batch;
+  const bool fp32 = real_kind == 1, many = K >= 11;
+  if (K < 3) return 1;
+  bool split;
+  if (fp32 && n == 256 && interp != kInterpLinear) split = many && fill <= 512;
+  else if (fill <= 512) split = true;
+  else if (interp == kInterpLinear) split = (fp32 && n == 256) || (many && (fill <= 1024 || (fp32 && n == 512)));
+  else if (interp == kInterpLagrange) split = fill <= 1024 && n <= (fp32 ? 128 : 256);
+  else split = fp32 && many && fill <= 1024;
+  return split ? kCombineSplits : 1;
 }
 
 bool cols_use_gen(int real_kind, int n) { return !is_pow2_len(n) || (real_kind == 0 && n > 2048); }
-
 
 int tune_candidates(int real_kind, int kind, int n, int S, int mode, int K, PassTune* out, int max) {
   int cnt = 0;
@@ -1275,7 +1290,7 @@ struct CombineL {
       using C = CombCfg<R, N>;
       dim3 grid((a.rows + C::G - 1) / C::G, a.nrhs);
       if constexpr (combine_splits_fit<R, N>()) {
-        if (combine_splits(sizeof(R) == 8 ? 0 : 1, N, a.rows, a.K, a.tune) == kCombineSplits) {
+        if (combine_splits(sizeof(R) == 8 ? 0 : 1, N, a.rows, a.batch, a.K, interp_mode(a), a.tune) == kCombineSplits) {
           combine_launch<R, TO, N, ACC, kCombineSplits>(a, grid, st);
           return hipGetLastError();
         }
