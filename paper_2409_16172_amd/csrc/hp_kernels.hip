@@ -1322,11 +1322,27 @@ struct CombineL {
 };
 
 
+// Pass C's plan over mixed-radix rows.  Lagrange weights bound the kernel where its lines
+// fill the chip, and line splits then only repeat the records: up to four splits below 28k
+// threads, two below 72k, none above (applies with one / two / four splits: 200 x 320 FP64,
+// K = 19, one field (13k) 84 / 61 / 48 us, four (51k) 100 / 79 / 84; 576^2 FP32, K = 11, one
+// (41k) 84 / 65 / 90, two (83k) 95 / 100 / 135; 360 x 600 FP64, K = 7, sixteen (576k) 383 /
+// 442).  FP32 rows with radices above ten, which spill or run at two waves there, keep the
+// LDS lines in that mode (512 x 1296, K = 7, four fields: 119 us against 162; 1440^2 113
+// against 132, 1200 points equal).
+static bool combine_line_plan(const CombineArgs& a, LinePlan* lp) {
+  if (!make_line_plan(a.real_kind, a.n, kLineComb, a.rows, a.K, a.tune.tc, lp)) return false;
+  if (interp_mode(a) != kInterpLagrange) return true;
+  if (a.real_kind == 1 && lp->rm > kLineRadixLo) return false;
+  const long threads = (long)a.rows * a.batch * lp->T;
+  const int most = threads <= 28000 ? kLineSplits : threads <= 72000 ? 2 : 1;
+  return lp->splits <= most || make_line_plan(a.real_kind, a.n, kLineComb, a.rows, most, a.tune.tc, lp);
+}
+
 hipError_t launch_combine(const CombineArgs& a, hipStream_t st) {
   if (!is_pow2_len(a.n)) {
     LinePlan lp;
-    if (line_kernels(a.tune) && make_line_plan(a.real_kind, a.n, kLineComb, a.rows, a.K, a.tune.tc, &lp))
-      return launch_line_combine(lp, a, st);
+    if (line_kernels(a.tune) && combine_line_plan(a, &lp)) return launch_line_combine(lp, a, st);
     GenPlan gp;
     if (a.real_kind == 0
             ? !tuned_gen_plan(a.n, gen_e<double>(), gen_maxthr<double>(), a.tune, &gp, gen_smax<double>(kGenComb))

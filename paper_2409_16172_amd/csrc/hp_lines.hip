@@ -36,10 +36,15 @@ __device__ __forceinline__ void line_barrier() {
 // with radices up to kLineRadixLo, two above.  FP32: four and, in pass C with radices up
 // to 16, three (pass B takes its 29 spilled registers for the fourth wave: 1920 x 1500,
 // K = 19, 268 -> 233 us; pass C does not: 2400^2, K = 8, 52 us with three, 71 with four).
-__host__ __device__ constexpr int line_waves(bool fp64, int rm, int kind) {
-  return fp64 ? (rm <= kLineRadixLo ? 3 : 2) : (rm <= kLineRadixLo || kind == kLineSym ? 4 : 3);
+// Pass C in the other interpolation modes, whose records and weights take more registers,
+// gives a wave up where it would spill 28 to 288 bytes a lane (Lagrange 576^2 FP64, K = 15,
+// sixteen fields: 1450 -> 900 us; 512 x 1296 FP32, three fields: 269 -> 206).
+__host__ __device__ constexpr int line_waves(bool fp64, int rm, int kind, int im = kInterpLinear) {
+  const bool less = kind == kLineComb && (im == kInterpLagrange || (im == kInterpBilinear && fp64));
+  return fp64 ? (rm <= kLineRadixLo && !less ? 3 : 2)
+              : (rm <= kLineRadixLo || kind == kLineSym ? 4 : 3) - (less ? 1 : 0);
 }
-#define HP_LINE_WAVES(R, RM, KIND) __attribute__((amdgpu_waves_per_eu(line_waves(sizeof(R) == 8, RM, KIND))))
+#define HP_LINE_WAVES(R, RM, ...) __attribute__((amdgpu_waves_per_eu(line_waves(sizeof(R) == 8, RM, __VA_ARGS__))))
 
 enum LineStageKind { kStageFirst = 0, kStageMid = 1, kStageLast = 2 };
 
@@ -351,7 +356,7 @@ struct CombCtx {
 // sum of each point, L rows per workgroup (SPLIT: L / splits rows, each shared by
 // `splits` lines that take its nodes in turn, where the rows alone are too few).
 template <typename R, typename TO, bool ACC, int IM, int RM, bool SPLIT>
-__global__ __launch_bounds__(kLineMaxThr) HP_LINE_WAVES(R, RM, kLineComb) void k_line_combine(const cpx<R>* __restrict__ fields, size_t fs,
+__global__ __launch_bounds__(kLineMaxThr) HP_LINE_WAVES(R, RM, kLineComb, IM) void k_line_combine(const cpx<R>* __restrict__ fields, size_t fs,
                                                               size_t frs, const double* __restrict__ pos,
                                                               const uint64_t* __restrict__ rowmask,
                                                               cpx<TO>* __restrict__ out, size_t out_rs, int rows,
