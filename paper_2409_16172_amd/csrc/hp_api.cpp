@@ -768,10 +768,18 @@ struct ApplyWs {
 // Fields of a batch that passes B, M and C take at once.  Where a field fills the chip by
 // itself and its used node rows fit the 256 MiB Infinity Cache (and a batch's do not), they
 // run the batch in parts that reuse the same node-field memory, so that passes M and C find
-// in the cache what pass B wrote (128^3 x 4 mixed, K = 19: 802 -> 695 us).  The results do
-// not depend on it.
+// in the cache what pass B wrote.  The results do not depend on it.  Powers of two, in 3-D
+// or in FP64 with columns of up to 1024 points; two, four or eight fields, whole / in parts:
+// 3-D 1.02-1.2 (128^3 mixed, K = 19, four fields 795 -> 677 us; Lagrange 64 x 64 x 512 0.98
+// at worst), FP64 1024^2 and rows of 2048 points 1.03-1.47.  Elsewhere a part's last
+// workgroups leave more of the chip idle than the cache saves: FP64 columns of 2048 points
+// 0.90-1.12, mixed 2-D 0.82-1.13, mixed-radix grids 0.81-1.15 (1200 x 960 FP64, K = 19,
+// eight fields 1512 -> 1856 us).
 int batch_part(const hp_plan_s* P, int nrhs) {
   constexpr double kCache = 256.0 * (1 << 20);
+  for (int d = 0; d < P->dim; ++d)
+    if (!hp::is_pow2_len(P->n[d])) return nrhs;
+  if (P->dim == 2 && (P->prec != HP_FP64 || P->n[0] > 1024)) return nrhs;
   const double one = P->slabs_used * (double)(P->npts / P->n[0]) * (double)P->fsize();
   if (P->npts < ((size_t)1 << 20) || one > kCache || one * nrhs <= kCache) return nrhs;
   return std::max(1, (int)(kCache / one));
