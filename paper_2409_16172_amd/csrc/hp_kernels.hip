@@ -1490,6 +1490,16 @@ __global__ __launch_bounds__(256) void k_stencil(const cpx<TI>* __restrict__ u, 
 // TB/s).
 constexpr int kStencilRows = 4;
 constexpr size_t kStencilRowsMin = (size_t)1 << 18;   // smaller grids need every thread
+// The kernel above, one point per thread, is the better one where a row takes about a
+// multiple of eight of its workgroups: the rows above and below a workgroup's points then
+// belong to workgroups of the same XCD and come from its L2 (2048^2 FP64 37.7 us, 41.5 with
+// four rows per thread; 1024 x 4050 39.1 and 41.8; mixed 1024 x 4096 20.4 and 20.8).  Off
+// by more than 104 points (64 in FP32) the two are level (FP64 1944: 40.3 and 41.0, 2160:
+// 34.3 and 34.2) or it loses (1800: 41.8 and 34.1).
+static bool stencil_rows_fit(const StencilArgs& a, size_t npts) {
+  const int n1 = a.n[1], off = n1 % 2048, band = a.kind == 0 || a.kind == 3 ? 104 : 64;
+  return a.dim == 2 && npts >= kStencilRowsMin && (n1 < 1024 || (off > band && off < 2048 - band));
+}
 template <typename R, typename TI, typename TO, bool RESID>
 __global__ __launch_bounds__(256) void k_stencil_rows(const cpx<TI>* __restrict__ u, cpx<TO>* __restrict__ y,
                                                       const cpx<R>* __restrict__ coef,
@@ -1538,7 +1548,7 @@ __global__ __launch_bounds__(256) void k_stencil_rows(const cpx<TI>* __restrict_
 
 hipError_t launch_stencil(const StencilArgs& a, hipStream_t st) {
   const size_t npts = (size_t)a.n[0] * a.n[1] * (a.dim == 3 ? a.n[2] : 1);
-  if (a.dim == 2 && npts >= kStencilRowsMin) {
+  if (stencil_rows_fit(a, npts)) {
     const size_t thr = (size_t)((a.n[0] + kStencilRows - 1) / kStencilRows) * a.n[1];
     auto go = [&](auto kern, auto* u, auto* y, auto* coef) {
       using R = decltype(coef->re);

@@ -35,3 +35,45 @@ def test_stencil_rows_match_oracle(orc, hp, shape, precision):
     for k in range(2):
         assert rel(y[k], ref.matvec(u[k])) < (1e-13 if precision == "fp64" else 1e-6)
     plan.close()
+
+
+# the other forms of the kernel, through the calls that take them: the FP64 residual f - P x
+# (a solve that ends at its initial guess reports its norm) and, in mixed precision on grids
+# past 2^20 points, the product that the Krylov steps store in FP64 (Arnoldi relation); rows
+# of 2048 points and near it go one point per thread
+@pytest.mark.parametrize("shape", [(512, 512), (486, 600), (4800, 60), (150, 2048), (144, 1944), (144, 2160)])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_residual_matches_oracle(orc, hp, shape, precision):
+    print(f"[case] stencil rows residual {shape} {precision}", flush=True)
+    rng = np.random.default_rng(sum(shape) + 1)
+    omega = 2 * np.pi * min(shape) / 8
+    c = 0.8 + 0.4 * rng.random(shape)
+    a = omega * (0.05 + 0.1 * rng.random(shape))
+    kw = dict(m_real=3, a_floor=0.05 * omega)
+    plan = hp.Plan(shape, omega, c, a, None, precision=precision, **kw)
+    ref = orc.Problem(shape, omega, c, a, None, **kw)
+    x = rng.standard_normal(shape) + 1j * rng.standard_normal(shape)
+    f = rng.standard_normal(shape) + 1j * rng.standard_normal(shape)
+    _, info = plan.solve(torch.from_numpy(f).to("cuda"), torch.from_numpy(x).to("cuda"), rtol=1e30)
+    want = np.linalg.norm(f - ref.matvec(x)) / np.linalg.norm(f)
+    assert info[0].iters == 0
+    assert abs(info[0].rel_true_residual - want) < 1e-13 * want
+    plan.close()
+
+
+@pytest.mark.parametrize("shape", [(1080, 1000), (540, 2048)])
+def test_mixed_product_of_large_grids(hp, shape):
+    print(f"[case] stencil rows mixed product {shape}", flush=True)
+    rng = np.random.default_rng(sum(shape))
+    omega = 2 * np.pi * min(shape) / 8
+    c = 0.8 + 0.4 * rng.random(shape)
+    plan = hp.Plan(shape, omega, c, np.full(shape, 0.1 * omega), None, m_real=3, a_floor=0.05 * omega, precision="mixed")
+    v0 = torch.from_numpy(rng.standard_normal(shape) + 1j * rng.standard_normal(shape)).to("cuda")
+    H, steps = plan.arnoldi(v0, 4, side="right")
+    V = torch.stack([plan.arnoldi_vector(np.eye(4)[k]).reshape(-1) for k in range(4)])
+    for k in range(3):
+        w = plan.matvec(plan.apply(V[k].reshape(shape).to(torch.complex64))).reshape(-1).to(torch.complex128)
+        gap = w - torch.from_numpy(H[:4, k]).to("cuda") @ V
+        # both sides apply the same FP32 operators to FP32 roundings of the same vector
+        assert float(gap.norm()) < 1e-5 * float(w.norm()), k
+    plan.close()
