@@ -373,7 +373,9 @@ hp_status hp_plan_pass_times(hp_plan p, double* ms, int cap, int* count);
  * every apply, solve step and session.
  * Only the radix schedule and the node splits change results (rounding).
  * If the environment variable HP_TUNE_CACHE names a file the choices are appended
- * to it, and hp_plan_create reads it for plans of the same grid, precision and K.
+ * to it, and hp_plan_create reads it for plans of the same grid, precision and K.  An
+ * entry with threads per line or a radix schedule means a line held in LDS, for any
+ * length (results are then that line's, to rounding); choices that do not fit are ignored.
  * before_ms / after_ms (may be NULL): the summed per-pass apply time before and
  * after.  Allocates two temporary device fields; blocks (a few hundred applies). */
 hp_status hp_plan_autotune(hp_plan p, double* before_ms, double* after_ms, void* stream);

@@ -61,8 +61,8 @@ __host__ __device__ constexpr int sweep_blocks(size_t npts) {
 }
 
 // Mixed-radix lines held in LDS: those the register lines below do not take (lengths
-// without four radices of at most 16, FP64 column passes over powers of two above 2048)
-// and radix schedules 1 to 3 of a tuning file.  Stage radices in order, threads per line
+// without four radices of at most 16, FP64 column passes over powers of two above 2048,
+// FP32 Lagrange rows with radices above ten) and the schedules a tuning file asks for.  Stage radices in order, threads per line
 // and (column passes) lines per workgroup.  A thread holds at most E elements of a line: kGenRowE in pass A, gen_e<R>() in the
 // column passes and in pass C.
 constexpr int kGenRowE = 16;
@@ -152,8 +152,8 @@ int line_stage_table(int real_kind, int n, int kind, std::vector<int>* index);
 int line_symbol_threads(int real_kind, int n, int* elems);
 
 // Run-time choices of a transform pass (0 = the built-in choice): threads per line and
-// radix schedule of mixed-radix lines held in LDS (register lines have one of each),
-// lines per workgroup of either kind,
+// radix schedule of mixed-radix lines held in LDS (either one asked for means such a line;
+// register lines have one of each), lines per workgroup of either kind,
 // node groups per column tile of the power-of-two symbol pass, node splits (1 or 4)
 // of the power-of-two pass C.  Only the radix schedule and the node splits change
 // results (rounding: the order of the node sum).

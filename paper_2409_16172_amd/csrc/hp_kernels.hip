@@ -957,9 +957,17 @@ bool make_gen_plan(int n, int E, int maxthr, GenPlan* gp, int order, int nthr_re
   return false;
 }
 
-// Whether a mixed-radix pass takes the register lines (hp_lines.hip), which have one
-// schedule per length; the other schedules a tuning file may ask for run in LDS.
-static bool line_kernels(const PassTune& t) { return t.order < 1 || t.order >= kGenOrders; }
+// Whether a tuning file asks for a schedule of the LDS lines that fits: threads per line or
+// a radix order other than the first.  The register lines (hp_lines.hip) have one schedule
+// per length and take the pass otherwise; a file's lines per workgroup (tc) alone are theirs.
+static bool lds_lines_asked(const PassTune& t, int n, int E, int maxthr, int smax) {
+  GenPlan g;
+  return (t.nthr > 0 || t.order > 0) && t.order < kGenOrders && make_gen_plan(n, E, maxthr, &g, t.order, t.nthr, smax);
+}
+template <typename R>
+static bool lds_lines_asked(const PassTune& t, int n, int kind) {
+  return lds_lines_asked(t, n, gen_e<R>(), gen_maxthr<R>(), gen_smax<R>(kind));
+}
 
 // A pass's plan with its run-time choices, or the built-in one when they do not fit.
 static bool tuned_gen_plan(int n, int E, int maxthr, const PassTune& t, GenPlan* gp, int smax) {
@@ -1181,7 +1189,8 @@ hipError_t launch_rows_fwd(int real_kind, int in_kind, int n, const void* in, vo
                            const PassTune& tune, hipStream_t st, const hipEvent_t* tev) {
   if (!is_pow2_len(n)) {
     LinePlan lp;
-    if (line_kernels(tune) && make_line_plan(real_kind, n, kLineRows, rows, 1, tune.tc, &lp))
+    if (!lds_lines_asked(tune, n, kGenRowE, 512, gen_rows_smax(real_kind, n)) &&
+        make_line_plan(real_kind, n, kLineRows, rows, 1, tune.tc, &lp))
       return launch_line_rows(real_kind, in_kind, lp, in, out, rows, in_rs, out_rs, nrhs, tw, skip, st, tev);
     GenPlan gp;
     if (!tuned_gen_plan(n, kGenRowE, 512, tune, &gp, gen_rows_smax(real_kind, n))) return hipErrorInvalidValue;
@@ -1243,7 +1252,8 @@ struct ColsL {
 hipError_t launch_cols(const ColsArgs& a, hipStream_t st) {
   if (cols_use_gen(a.real_kind, a.n)) {
     LinePlan lp;
-    if (line_kernels(a.tune) &&
+    const int gk = a.mode == 1 ? kGenSym : kGenCols;
+    if (!(a.real_kind == 0 ? lds_lines_asked<double>(a.tune, a.n, gk) : lds_lines_asked<float>(a.tune, a.n, gk)) &&
         make_line_plan(a.real_kind, a.n, a.mode == 1 ? kLineSym : kLineCols, a.S,
                        a.mode == 1 ? a.K : a.outer * a.nfields, a.tune.tc, &lp) &&
         (a.mode != 1 || a.store_mask_thr == a.n / lp.r[0]))
@@ -1342,7 +1352,9 @@ static bool combine_line_plan(const CombineArgs& a, LinePlan* lp) {
 hipError_t launch_combine(const CombineArgs& a, hipStream_t st) {
   if (!is_pow2_len(a.n)) {
     LinePlan lp;
-    if (line_kernels(a.tune) && combine_line_plan(a, &lp)) return launch_line_combine(lp, a, st);
+    if (!(a.real_kind == 0 ? lds_lines_asked<double>(a.tune, a.n, kGenComb) : lds_lines_asked<float>(a.tune, a.n, kGenComb)) &&
+        combine_line_plan(a, &lp))
+      return launch_line_combine(lp, a, st);
     GenPlan gp;
     if (a.real_kind == 0
             ? !tuned_gen_plan(a.n, gen_e<double>(), gen_maxthr<double>(), a.tune, &gp, gen_smax<double>(kGenComb))

@@ -92,3 +92,34 @@ def test_lines_per_workgroup_keep_results(hp, shape, precision, tmp_path, monkey
         monkeypatch.setenv("HP_TUNE_CACHE", str(path))
         assert torch.equal(make().apply(v), u0)
         monkeypatch.delenv("HP_TUNE_CACHE")
+
+
+@pytest.mark.parametrize("order,nthr", [(0, 128), (1, 0), (2, 0), (3, 0), (0, 192), (2, 128)])
+@pytest.mark.parametrize("shape,precision", [((360, 240), "fp64"), ((240, 600), "mixed"), ((20, 60, 90), "fp64")])
+def test_files_with_lds_schedules_keep_them(hp, shape, precision, order, nthr, tmp_path, monkeypatch):
+    """A tuning file that names threads per line or a radix order means the LDS lines, as it
+    did before lines were held in registers: the result is theirs, to rounding that of the
+    register lines but not bit for bit, and lines per workgroup beside them change nothing."""
+    print(f"[case] LDS schedules {shape} {precision} {order} {nthr}", flush=True)
+    omega = 2 * np.pi * min(shape) / 6
+    c = inputs.gaussian_random_field(shape, 5.0, 9)
+    a = np.full(shape, 0.05 * omega)
+    make = lambda: hp.Plan(shape, omega, c, a, None, m_real=6, precision=precision)  # noqa: E731
+    dt = torch.complex128 if precision == "fp64" else torch.complex64
+    rng = np.random.default_rng(4)
+    v = torch.from_numpy(rng.standard_normal(shape) + 1j * rng.standard_normal(shape)).to("cuda").to(dt)
+    u0 = make().apply(v)
+    n = list(shape) + [1] * (3 - len(shape))
+    got = []
+    for tc in (0, 2):
+        path = tmp_path / f"tune{tc}.txt"
+        path.write_text("".join(f"hp-tune {len(shape)} {n[0]} {n[1]} {n[2]} {int(precision != 'fp64')} 6 {s} {nthr} {tc} "
+                                f"{order} 0\n" for s in range(5)))
+        monkeypatch.setenv("HP_TUNE_CACHE", str(path))
+        plan = make()
+        monkeypatch.delenv("HP_TUNE_CACHE")
+        assert plan.info()["tune"] == [(nthr, tc, order, 0)] * 5
+        got.append(plan.apply(v))
+        assert rel(got[-1].cpu().numpy(), u0.cpu().numpy()) < (1e-12 if precision == "fp64" else 1e-5)
+        assert not torch.equal(got[-1], u0)
+    assert torch.equal(got[0], got[1])
