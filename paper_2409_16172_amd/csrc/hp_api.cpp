@@ -97,6 +97,7 @@ struct hp_plan_s {
   std::vector<hipEvent_t> timer_ev;   // 2 per launch, created on demand and reused
 
   int real_kind() const { return prec == HP_FP64 ? 0 : 1; }
+  int interp() const { return Ma >= 2 ? 2 : (order >= 2 ? 1 : 0); }   // InterpMode of the combine
   size_t fsize() const { return prec == HP_FP64 ? 16 : 8; }
   const void* tw(int axis) const { return prec == HP_FP64 ? tw64[axis].p : tw32[axis].p; }
   // the stage table behind the n[axis] roots (mixed-radix lines of passes B and C)
@@ -785,6 +786,12 @@ int batch_part(const hp_plan_s* P, int nrhs) {
   return std::max(1, (int)(kCache / one));
 }
 
+// Node splits of the plan's pass C under the choice t.
+int pass_c_splits(const hp_plan_s* P, const hp::PassTune& t) {
+  const int nl = P->n[P->dim - 1];
+  return hp::combine_splits(P->real_kind(), nl, (int)(P->npts / nl), batch_part(P, P->max_nrhs), P->K, P->interp(), t);
+}
+
 // Passes A and A' of an apply over nrhs fields: their spectra along the last axes, into wt.
 // can_time: the pass timer may create events (here and in apply_back).
 hipError_t apply_front(hp_plan_s* P, const void* v, int in_kind, size_t in_rs, int nrhs, const int* skip,
@@ -1441,11 +1448,11 @@ struct Session {
 
   // This session's current Arnoldi step as a member of a grouped launch, when the
   // grouped kernels take it: one right-hand side, right preconditioning, the FP32
-  // preconditioner, grids of at most kGroupMaxPts points with power-of-two lines the
-  // grouped passes cover, and the combine's built-in workgroup shape.
+  // preconditioner, and grids of at most kGroupMaxPts points with power-of-two lines the
+  // grouped passes cover.
   bool group_member(hp::GroupMember* g) const {
-    if (o.side != HP_RIGHT || arnoldi_only || nrhs != 1 || P->prec != HP_MIXED || P->tune[4].ng > 1 ||
-        W->z.p == nullptr || P->npts > kGroupMaxPts)
+    if (o.side != HP_RIGHT || arnoldi_only || nrhs != 1 || P->prec != HP_MIXED || W->z.p == nullptr ||
+        P->npts > kGroupMaxPts)
       return false;
     hp::GroupMember m{};
     m.dim = P->dim;
@@ -1457,7 +1464,7 @@ struct Session {
     m.mo = P->mo;
     m.order = P->order;
     m.Ma = P->Ma;
-    m.interp = P->Ma >= 2 ? 2 : (P->order >= 2 ? 1 : 0);
+    m.interp = P->interp();
     m.scale = 1.0 / (double)P->npts;
     for (int d = 0; d < P->dim; ++d) m.tw[d] = P->tw(d);
     m.lam_ax = (const double*)P->lam_ax.p;
@@ -1486,9 +1493,7 @@ struct Session {
     m.j = j;
     m.restart = o.restart;
     m.ng_b = P->tune[2].ng;
-    const int nl = P->n[P->dim - 1];
-    m.splits = hp::combine_splits(P->real_kind(), nl, (int)(P->npts / nl), batch_part(P, P->max_nrhs), P->K, m.interp,
-                                  P->tune[4]);
+    m.splits = pass_c_splits(P, P->tune[4]);
     if (!hp::group_member_ok(m)) return false;
     *g = m;
     return true;
@@ -1821,8 +1826,12 @@ hp_status hp_plan_autotune(hp_plan p, double* before_ms, double* after_ms, void*
     if (!slots[sl].used) continue;
     hp::PassTune cand[64];
     const int nc = hp::tune_candidates(rk, slots[sl].kind, slots[sl].n, slots[sl].S, slots[sl].mode, p->K, cand, 64);
-    hp::PassTune best = p->tune[sl];
+    const hp::PassTune now = p->tune[sl];
+    hp::PassTune best = now;
     for (int c = 0; c < nc; ++c) {
+      // node splits that the plan takes by itself are no choice of their own, nor is the present one
+      if (sl == 4 && cand[c].ng > 0 && cand[c].ng == pass_c_splits(p, hp::PassTune{})) cand[c].ng = 0;
+      if (cand[c] == now) continue;
       p->tune[sl] = cand[c];
       double t[5];
       HP_TRY(measure(t));

@@ -159,6 +159,7 @@ int line_symbol_threads(int real_kind, int n, int* elems);
 // results (rounding: the order of the node sum).
 struct PassTune {
   int nthr = 0, tc = 0, order = 0, ng = 0;
+  bool operator==(const PassTune& o) const { return nthr == o.nthr && tc == o.tc && order == o.order && ng == o.ng; }
 };
 // slot kinds of the candidates below: 0 pass A (rows forward), 1 column pass (B, A', M),
 // 2 pass C (rows inverse + combine)

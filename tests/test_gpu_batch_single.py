@@ -74,3 +74,46 @@ def test_grouped_solves_equal_batch(hp):
         s.close()
     for p in plans:
         p.close()
+
+
+@pytest.mark.parametrize("ng", [0, 1, 4])
+@pytest.mark.parametrize("m_real", [5, 12])
+def test_any_node_splits_step_in_groups(hp, ng, m_real, tmp_path, monkeypatch):
+    """A tuned number of node splits, also the one that the plan takes by itself, leaves a
+    session in the grouped launches (which the pass timer does not record, as it does the
+    plan's own) and its solve bitwise that of a batch."""
+    print(f"[case] grouped node splits {ng} {m_real}", flush=True)
+    shapes = [(512, 512), (256, 1024)]
+    path = tmp_path / "tune.txt"
+    path.write_text("".join(f"hp-tune 2 {s[0]} {s[1]} 1 1 {m_real} 4 0 0 0 {ng}\n" for s in shapes))
+    monkeypatch.setenv("HP_TUNE_CACHE", str(path))
+    plans = [_plan(hp, s, m_real, 2) for s in shapes]
+    monkeypatch.delenv("HP_TUNE_CACHE")
+    fs = [_sources(s, 2) for s in shapes]
+    opts = dict(restart=6, rtol=1e-12, max_cycles=1)
+    want = [p.solve(f, **opts)[0][0] for p, f in zip(plans, fs)]
+    solvers = [hp.Solver(p, 1, **opts) for p in plans]
+    for p, s, f in zip(plans, solvers, fs):
+        assert p.info()["tune"][4][3] == ng
+        s.start(f[0].contiguous())
+        p.time_pass(2)
+    left = list(solvers)
+    for _ in range(100000):
+        left = [s for s, d in zip(left, hp.advance_group(left, 2)) if not d]
+        if not left:
+            break
+    for p, s, w in zip(plans, solvers, want):
+        assert torch.equal(s.result()[0].reshape(w.shape), w)
+        assert len(p.pass_times()) <= 2     # start and end of the cycle, no step
+        s.close()
+        p.close()
+
+
+@pytest.mark.parametrize("shape,m_real,nrhs,own", [((256, 256), 12, 1, 4), ((512, 512), 5, 8, 1)])
+def test_autotuner_leaves_the_own_node_splits(hp, shape, m_real, nrhs, own):
+    print(f"[case] autotuned node splits {shape} {m_real} x{nrhs}", flush=True)
+    plan = _plan(hp, shape, m_real, nrhs)
+    for _ in range(3):
+        plan.autotune()
+        assert plan.info()["tune"][4][3] != own
+    plan.close()
