@@ -337,7 +337,8 @@ hp_status hp_solver_destroy(hp_solver s);
  * out-of-place pass `reps` times back to back between two HIP events on
  * `stream` (the in-place 3-D middle-axis passes once).  u holds Q_M v on
  * return.  Blocks until done.  ms[5] receives the average milliseconds per
- * launch of the passes in order
+ * launch (of a batch whose passes run in parts, see hp_plan_time_pass: the sum over
+ * its parts) of the passes in order
  *   0: forward transform along the last (contiguous) axis
  *   1: forward transform along the middle axis (3-D only, else 0)
  *   2: forward transform along axis 0, symbol multiplies and inverse transforms
@@ -358,7 +359,9 @@ hp_status hp_profile_apply(hp_plan p, const void* v, void* u, int nrhs, int reps
  * Launches captured into a graph and launches beyond 65536 per read are not
  * timed.  hp_plan_pass_times waits for the recorded launches, stores the
  * milliseconds of each in launch order in ms[0..min(count, cap)-1], sets *count
- * to the number recorded and clears the record.  A launch whose right-hand sides
+ * to the number recorded and clears the record.  A batch whose node fields outgrow the
+ * GPU's last-level cache may run passes 2 to 4 in parts, a launch each: the launches of
+ * one pass of an apply are one entry, their times added.  A launch whose right-hand sides
  * had all stopped returns at once and is recorded too (a few microseconds).  The
  * events are created on demand and kept until hp_plan_destroy. */
 hp_status hp_plan_time_pass(hp_plan p, int slot);

@@ -93,7 +93,9 @@ struct hp_plan_s {
   struct SolverWs* inner_ws_ptr = nullptr;   // the inner solves of hp_arnoldi's inverse operators
   // pass timer (hp_plan_time_pass): the start and end times of every launch of one pass
   int timer_slot = -1;
-  size_t timer_n = 0;                 // launches recorded since the last read
+  size_t timer_n = 0;                 // launches timed since the last read
+  std::vector<size_t> timer_rec;      // the first launch of each entry (the parts of a batch share one)
+  bool timer_open = false;            // the last entry takes the batch's further parts
   std::vector<hipEvent_t> timer_ev;   // 2 per launch, created on demand and reused
 
   int real_kind() const { return prec == HP_FP64 ? 0 : 1; }
@@ -730,17 +732,25 @@ constexpr bool kFusePassA = HP_FUSE_PASS_A != 0;
 // Pass timer: launches recorded per read at most (later ones are not timed).
 constexpr size_t kMaxTimedLaunches = 1 << 16;
 
-// Timing events for the next launch of the timed pass on st (nullptr when the
-// launch is not timed: a graph capture, or the record is full).
-hipError_t timer_events(hp_plan_s* P, hipStream_t st, const hipEvent_t** tev) {
+// Timing events for the next launch of the timed pass on st, part `part` of `parts` of its
+// batch (nullptr when the launch is not timed: a graph capture, or the record is full).
+hipError_t timer_events(hp_plan_s* P, hipStream_t st, int part, int parts, const hipEvent_t** tev) {
   *tev = nullptr;
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  hipError_t e = hipStreamIsCapturing(st, &cs);
-  if (e != hipSuccess) return e;
-  if (cs != hipStreamCaptureStatusNone || P->timer_n >= kMaxTimedLaunches) return hipSuccess;
+  if (part == 0) {
+    P->timer_open = false;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    const hipError_t e = hipStreamIsCapturing(st, &cs);
+    if (e != hipSuccess) return e;
+    if (cs != hipStreamCaptureStatusNone || P->timer_n + (size_t)parts > kMaxTimedLaunches) return hipSuccess;
+    P->timer_rec.push_back(P->timer_n);
+    P->timer_open = true;
+  } else if (!P->timer_open) {
+    return hipSuccess;
+  }
   while (P->timer_ev.size() < 2 * (P->timer_n + 1)) {
     hipEvent_t ev;
-    if ((e = hipEventCreate(&ev)) != hipSuccess) return e;
+    const hipError_t e = hipEventCreate(&ev);
+    if (e != hipSuccess) return e;
     P->timer_ev.push_back(ev);
   }
   *tev = &P->timer_ev[2 * P->timer_n];
@@ -750,10 +760,10 @@ hipError_t timer_events(hp_plan_s* P, hipStream_t st, const hipEvent_t** tev) {
 
 // Launch of pass `slot`, with the timer's events when that pass is timed.
 template <typename F>
-hipError_t timed_pass(hp_plan_s* P, int slot, bool can_time, hipStream_t st, F&& launch) {
+hipError_t timed_pass(hp_plan_s* P, int slot, bool can_time, hipStream_t st, int part, int parts, F&& launch) {
   const hipEvent_t* tev = nullptr;
   if (P->timer_slot == slot && can_time) {
-    const hipError_t e = timer_events(P, st, &tev);
+    const hipError_t e = timer_events(P, st, part, parts, &tev);
     if (e != hipSuccess) return e;
   }
   return launch(tev);
@@ -802,7 +812,7 @@ hipError_t apply_front(hp_plan_s* P, const void* v, int in_kind, size_t in_rs, i
   const int nl = P->n[P->dim - 1];
   const int rows = (int)(np / nl);
   for (int r = 0; r < reps; ++r) {
-    e = timed_pass(P, 0, can_time, st, [&](const hipEvent_t* tev) {
+    e = timed_pass(P, 0, can_time, st, 0, 1, [&](const hipEvent_t* tev) {
       return hp::launch_rows_fwd(rk, in_kind, nl, v, wt, rows, in_rs, np, nrhs, P->tw(P->dim - 1), skip,
                                  P->tune[0], st, tev);
     });
@@ -815,16 +825,18 @@ hipError_t apply_front(hp_plan_s* P, const void* v, int in_kind, size_t in_rs, i
     m.in = wt; m.out = wt; m.S = P->n[2]; m.outer = P->n[0]; m.nfields = 1; m.nrhs = nrhs;
     m.in_rs = np; m.out_rs = np; m.in_fs = np; m.out_fs = np; m.tw = P->tw(1); m.skip = skip;
     m.tune = P->tune[1];
-    if ((e = timed_pass(P, 1, can_time, st, [&](const hipEvent_t* tev) { m.tev = tev; return hp::launch_cols(m, st); })) != hipSuccess)
+    if ((e = timed_pass(P, 1, can_time, st, 0, 1, [&](const hipEvent_t* tev) { m.tev = tev; return hp::launch_cols(m, st); })) != hipSuccess)
       return e;
     if (ev && (e = hipEventRecord(ev[2], st)) != hipSuccess) return e;
   }
   return hipSuccess;
 }
 
-// Passes B, M and C over nrhs fields whose spectra are in wt, with their node fields in wf.
+// Passes B, M and C over nrhs fields whose spectra are in wt, with their node fields in wf:
+// part `part` of `parts` of the batch.
 hipError_t apply_back(hp_plan_s* P, void* u, int out_kind, size_t out_rs, bool acc, int nrhs, const int* skip,
-                      hipStream_t st, hipEvent_t* ev, int reps, void* const wt, void* const wf, bool can_time) {
+                      hipStream_t st, hipEvent_t* ev, int reps, void* const wt, void* const wf, bool can_time,
+                      int part, int parts) {
   const int rk = P->real_kind();
   const size_t np = P->npts;
   hipError_t e;
@@ -841,7 +853,7 @@ hipError_t apply_back(hp_plan_s* P, void* u, int out_kind, size_t out_rs, bool a
   b.store_need = (const uint8_t*)P->slabneed.p;
   b.tune = P->tune[2];
   for (int r = 0; r < reps; ++r)
-    if ((e = timed_pass(P, 2, can_time, st, [&](const hipEvent_t* tev) { b.tev = tev; return hp::launch_cols(b, st); })) != hipSuccess)
+    if ((e = timed_pass(P, 2, can_time, st, part, parts, [&](const hipEvent_t* tev) { b.tev = tev; return hp::launch_cols(b, st); })) != hipSuccess)
       return e;
   if (ev && (e = hipEventRecord(ev[0], st)) != hipSuccess) return e;
   if (P->dim == 3) {   // inverse along the middle axis for the K fields, in place
@@ -851,7 +863,7 @@ hipError_t apply_back(hp_plan_s* P, void* u, int out_kind, size_t out_rs, bool a
     m.in_rs = np * P->K; m.out_rs = np * P->K; m.in_fs = np; m.out_fs = np; m.tw = P->tw(1); m.skip = skip;
     m.slab_need = (const uint8_t*)P->slabneed.p;
     m.tune = P->tune[3];
-    if ((e = timed_pass(P, 3, can_time, st, [&](const hipEvent_t* tev) { m.tev = tev; return hp::launch_cols(m, st); })) != hipSuccess)
+    if ((e = timed_pass(P, 3, can_time, st, part, parts, [&](const hipEvent_t* tev) { m.tev = tev; return hp::launch_cols(m, st); })) != hipSuccess)
       return e;
     if (ev && (e = hipEventRecord(ev[1], st)) != hipSuccess) return e;
   }
@@ -864,7 +876,7 @@ hipError_t apply_back(hp_plan_s* P, void* u, int out_kind, size_t out_rs, bool a
   c.posa = (const double*)P->posa.p; c.Ma = P->Ma;
   c.tune = P->tune[4];
   for (int r = 0; r < (acc ? 1 : reps); ++r)
-    if ((e = timed_pass(P, 4, can_time, st, [&](const hipEvent_t* tev) { c.tev = tev; return hp::launch_combine(c, st); })) != hipSuccess)
+    if ((e = timed_pass(P, 4, can_time, st, part, parts, [&](const hipEvent_t* tev) { c.tev = tev; return hp::launch_combine(c, st); })) != hipSuccess)
       return e;
   return ev ? hipEventRecord(ev[2], st) : hipSuccess;
 }
@@ -873,7 +885,7 @@ hipError_t apply_back(hp_plan_s* P, void* u, int out_kind, size_t out_rs, bool a
 // in_kind/out_kind: 0 = complex128, 1 = complex64.  Every field's passes A and A' come
 // before the first write to u, so u may overlap v in any way.
 // ev, reps (profiling only, with acc false): events recorded before pass A, after it and
-// (3-D) after A', after B, (3-D) after M, and after C, over the whole batch; the
+// (3-D) after A', and for each part of the batch after B, (3-D) after M, and after C; the
 // out-of-place passes A, B and C are launched reps times back to back between their
 // events; they read and write disjoint buffers, so a repeat recomputes the same result.
 // The in-place middle-axis passes of 3-D grids are launched once.
@@ -890,11 +902,12 @@ hipError_t run_apply(hp_plan_s* P, const void* v, int in_kind, size_t in_rs, voi
   if (ev && (e = hipEventRecord(ev[0], st)) != hipSuccess) return e;
   if (!from_b && (e = apply_front(P, v, in_kind, in_rs, nrhs, skip, st, ev, reps, wt, can_time)) != hipSuccess)
     return e;
-  const int part = ev ? nrhs : batch_part(P, nrhs);
+  const int per = batch_part(P, nrhs), parts = (nrhs + per - 1) / per;
   const size_t fb = P->npts * P->fsize(), ob = out_rs * (out_kind == 0 ? 16 : 8);
-  for (int r0 = 0; r0 < nrhs; r0 += part) {
-    e = apply_back(P, (char*)u + ob * r0, out_kind, out_rs, acc, std::min(part, nrhs - r0), skip ? skip + r0 : nullptr,
-                   st, ev ? ev + 3 : nullptr, reps, wt + fb * r0, wf, can_time);
+  for (int k = 0; k < parts; ++k) {
+    const int r0 = k * per;
+    e = apply_back(P, (char*)u + ob * r0, out_kind, out_rs, acc, std::min(per, nrhs - r0), skip ? skip + r0 : nullptr,
+                   st, ev ? ev + 3 + 3 * k : nullptr, reps, wt + fb * r0, wf, can_time, k, parts);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -905,12 +918,13 @@ hipError_t run_apply(hp_plan_s* P, const void* v, int in_kind, size_t in_rs, voi
 // caches), then every out-of-place pass reps times back to back between a pair of
 // events, so that an event pair brackets a run of launches of one kernel and the
 // per-launch figure is that kernel's duration (the in-place 3-D middle-axis passes run
-// once).
+// once).  The figures of a batch that runs in parts are the sums over its parts.
 hipError_t time_passes(hp_plan_s* p, const void* v, void* u, int nrhs, int reps, double* ms, hipStream_t st) {
   const int kind = p->prec == HP_FP64 ? 0 : 1;
+  const int per = batch_part(p, nrhs), parts = (nrhs + per - 1) / per;
   std::vector<hipEvent_t> ev;
   hipError_t err = hipSuccess;
-  while (err == hipSuccess && ev.size() < 6) {
+  while (err == hipSuccess && (int)ev.size() < 3 + 3 * parts) {
     hipEvent_t x;
     if ((err = hipEventCreate(&x)) == hipSuccess) ev.push_back(x);
   }
@@ -926,9 +940,12 @@ hipError_t time_passes(hp_plan_s* p, const void* v, void* u, int nrhs, int reps,
   const bool d3 = p->dim == 3;
   add(0, 0, 1, reps);
   if (d3) add(1, 1, 2, 1);
-  add(2, d3 ? 2 : 1, 3, reps);
-  if (d3) add(3, 3, 4, 1);
-  add(4, d3 ? 4 : 3, 5, reps);
+  for (int k = 0; k < parts; ++k) {
+    const int b = 3 + 3 * k;   // the part's events: after B, (3-D) after M, after C
+    add(2, k > 0 ? b - 1 : d3 ? 2 : 1, b, reps);
+    if (d3) add(3, b, b + 1, 1);
+    add(4, d3 ? b + 1 : b, b + 2, reps);
+  }
   for (hipEvent_t x : ev) (void)hipEventDestroy(x);
   for (int i = 0; i < 5; ++i) ms[i] = acc[i];
   return err;
@@ -1856,20 +1873,27 @@ hp_status hp_plan_time_pass(hp_plan p, int slot) {
   if (!p || slot < -1 || slot > 4) return HP_E_INVALID;
   p->timer_slot = slot;
   p->timer_n = 0;
+  p->timer_rec.clear();
+  p->timer_open = false;
   return HP_OK;
 }
 
 hp_status hp_plan_pass_times(hp_plan p, double* ms, int cap, int* count) {
   if (!p || !count || cap < 0 || (cap > 0 && !ms)) return HP_E_INVALID;
-  const size_t n = p->timer_n;
+  const size_t n = p->timer_rec.size(), launches = p->timer_n;
+  const std::vector<size_t> first = std::move(p->timer_rec);
+  p->timer_rec.clear();
   p->timer_n = 0;
+  p->timer_open = false;
   for (size_t i = 0; i < n; ++i) {
-    HP_TRY(hipEventSynchronize(p->timer_ev[2 * i + 1]));
-    if ((int)i < cap) {
+    double sum = 0;
+    for (size_t k = first[i]; k < (i + 1 < n ? first[i + 1] : launches); ++k) {
+      HP_TRY(hipEventSynchronize(p->timer_ev[2 * k + 1]));
       float t = 0;
-      HP_TRY(hipEventElapsedTime(&t, p->timer_ev[2 * i], p->timer_ev[2 * i + 1]));
-      ms[i] = (double)t;
+      if ((int)i < cap) HP_TRY(hipEventElapsedTime(&t, p->timer_ev[2 * k], p->timer_ev[2 * k + 1]));
+      sum += (double)t;
     }
+    if ((int)i < cap) ms[i] = sum;
   }
   *count = (int)n;
   return HP_OK;

@@ -39,3 +39,33 @@ def test_batch_parts_equal_single(hp, shape, precision, m_real, nrhs):
         xk, ik = plan.solve(f[k].contiguous(), rtol=1e-3, max_cycles=2, restart=5)
         assert torch.equal(x[k], xk) and ik[0].iters == info[k].iters
     plan.close()
+
+
+def test_pass_times_of_a_batch_in_parts(hp):
+    """A pass of a batch that runs in parts is one entry of the pass timer, as it is when the
+    batch runs whole, and the profile's figures cover all of its fields."""
+    print("[case] pass timer of batch parts", flush=True)
+    shape, nrhs = (1024, 1024), 3
+    omega = 2 * np.pi * min(shape) / 10
+    c = inputs.gaussian_random_field(shape, 4.0, 5)
+    plan = hp.Plan(shape, omega, c, np.full(shape, 0.05 * omega), None, m_real=12, max_nrhs=nrhs)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    v = torch.view_as_complex(torch.randn((nrhs,) + shape + (2,), generator=g, dtype=torch.float64, device="cuda"))
+    one = [plan.apply(v[k]) for k in range(nrhs)]
+    for slot in (0, 2, 4):
+        plan.time_pass(slot)
+        plan.apply(v)
+        plan.apply(v[0])
+        plan.apply(v)
+        t = plan.pass_times()
+        assert len(t) == 3 and min(t) > 0
+        # three fields take longer than one (by 1.5 at least: a field fills the chip)
+        assert min(t[0], t[2]) > 1.5 * t[1]
+    plan.time_pass(None)
+    u = torch.empty_like(v)
+    ms, _ = plan.profile_apply(v, out=u, reps=3)
+    assert all(torch.equal(u[k], one[k]) for k in range(nrhs))
+    ms1, _ = plan.profile_apply(v[0].contiguous(), reps=3)
+    for slot in (0, 2, 4):
+        assert ms[slot] > 1.5 * ms1[slot]
+    plan.close()
