@@ -159,8 +159,10 @@ __device__ __forceinline__ void symbol_mul(const cpx<R> (&v)[E], cpx<R> (&x)[CNT
 // node n.  Piecewise linear: the record p itself; the weight is the hat of width 1 around
 // the node's centre on the record's axis, n for a real node, -(i + 2) for layer node i,
 // and -1 beside its own for the background node mo, where the layer's leg starts (record
-// -(1 + j + t), see decode_pos).  The differences and 1 - |d| are exact in FP64, so the
-// weights are those of decode_pos, without a search or a compare per node.
+// -(1 + j + t), see decode_pos).  The weights are those of decode_pos to rounding, without
+// a search or a compare per node: the differences and 1 - |d| are exact in FP64 but in the
+// first segment, where p - 1 rounds by at most 2^-54; FP32 weights are rounded from FP64
+// one by one, not as a rounded t and 1 - t.
 // (FP32 rows above 1024 points keep the select: their combine has no registers left for
 // the FP64 temporaries, 2048^2 mixed 190 us with selects before, 208 with hats, 173 with
 // selects and the reordered loads)

@@ -2389,12 +2389,15 @@ __global__ __launch_bounds__(256) void k_arnoldi_update(cpx<double>* __restrict_
   }
 }
 
-// The same on grids of 4096 to 2^18 points: one point per thread and eight vectors in
-// flight, so that the launch has four times the workgroups and half the rounds of memory
-// latency (256^2 FP64 at j = 28: 10.0 -> 5.1 us).  Smaller grids keep the kernel above:
-// where its last workgroup's points round differently, a solve whose source and medium
-// are mirror images of themselves does not stay in the symmetric subspace, as the
-// oracle's does not (36^2 plain GMRES(64): 112 steps with either, 107 in exact symmetry).
+// The same on grids of 4096 (64^2, the smallest grid of the benchmark workloads) to 2^18
+// points: one point per thread and eight vectors in flight, so that the launch has four
+// times the workgroups and half the rounds of memory latency (256^2 FP64 at j = 28: 10.0 ->
+// 5.1 us).  Smaller grids would gain too (a cycle of 30 plain steps at 60 x 64 929 -> 832
+// us, at 24^2 867 -> 812) but keep the kernel above: here every point rounds alike, so that
+// a solve whose source and medium are mirror images of themselves stays in the symmetric
+// subspace, and the oracle's solves, whose step counts the smallest grids are held to, do
+// not (36^2 plain GMRES(64): 107 steps so, 112 in the oracle and with the kernel above,
+// whose last workgroup's points round differently).
 constexpr size_t kUpdSmallMin = 4096, kUpdSmallMax = (size_t)1 << 18;
 constexpr int kUpdSmallChunk = 8;
 __host__ __device__ constexpr bool update_small(size_t npts) { return npts >= kUpdSmallMin && npts < kUpdSmallMax; }
@@ -2521,7 +2524,8 @@ __global__ __launch_bounds__((RowCfg<double, N>::THREADS)) void k_arnoldi_update
 
 // The update of k_arnoldi_update for the grouped launches (bx, gx: this workgroup's
 // index among the gx of one right-hand side).  The single-plan kernel keeps its own
-// copy: its code, and so its rounding, stays exactly as it was.
+// copy, whose rounding the compiler's code decides; members of the sizes that
+// update_small names take arnoldi_update_small_body, one body for both.
 __device__ __forceinline__ void arnoldi_update_body(cpx<double>* __restrict__ V, size_t npts, size_t vrs,
                                                     const KState* __restrict__ state,
                                                     const int* __restrict__ skip_step, int j, int rhs, int bx,
