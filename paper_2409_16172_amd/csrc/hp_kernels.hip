@@ -1562,9 +1562,13 @@ hipError_t launch_stencil(const StencilArgs& a, hipStream_t st) {
   const size_t npts = (size_t)a.n[0] * a.n[1] * (a.dim == 3 ? a.n[2] : 1);
   if (stencil_rows_fit(a, npts)) {
     const size_t thr = (size_t)((a.n[0] + kStencilRows - 1) / kStencilRows) * a.n[1];
+    // a multiple of eight workgroups per right-hand side, so that one point's coefficients
+    // meet in one XCD's L2 for all of them (720 x 384 FP64 x 3, 270 workgroups: 10.4 us, 9.1
+    // with one point per thread)
+    const unsigned blocks = (unsigned)((thr + 255) / 256 + 7) / 8 * 8;
     auto go = [&](auto kern, auto* u, auto* y, auto* coef) {
       using R = decltype(coef->re);
-      hipLaunchKernelGGL(kern, dim3((unsigned)((thr + 255) / 256), a.nrhs), dim3(256), 0, st, u, y, coef,
+      hipLaunchKernelGGL(kern, dim3(blocks, a.nrhs), dim3(256), 0, st, u, y, coef,
                          (const cpx<double>*)a.f, a.n[0], a.n[1], (R)a.ih2[0], (R)a.ih2[1], a.u_rs, a.y_rs, a.skip);
       return hipGetLastError();
     };
