@@ -2126,12 +2126,18 @@ __device__ __forceinline__ void arnoldi_finalize(KState& S, const cpx<double>* p
 constexpr int kDotsTile = 1024;
 constexpr int kDotsBatch = 8;
 constexpr int kDotsSlots = 8;   // basis vectors per wave: j <= NW * kDotsSlots
-// Grids whose blocks hold at most 64 SP points keep all of them, of four basis vectors at
-// once, in flight (SP = 4; one memory latency for four vectors instead of one each: 256^2
-// FP64 sweep at j = 28, 19.4 -> 13.5 us).  A kernel of its own: those registers would cost
-// the larger grids a wave per SIMD.
+// One right-hand side on a grid whose blocks hold at most 64 SP points and leave the chip
+// idle (256 blocks, up to 2^16 points): all points of four basis vectors in flight (SP = 4;
+// one memory latency for four vectors instead of one each), with the sums in the same order
+// and bits.  A kernel of its own, whose registers cost the others waves: a cycle of 30 plain
+// steps takes 909 us without it and 853 with at 256^2 FP64, 867 and 819 at 128^2, but 1026
+// and 1080 at 300^2 (512 blocks), 1075 and 1129 for two right-hand sides at 256^2, 2333 and
+// 2728 for eight.
 constexpr int kDotsShort = 4;
-static bool sweep_short(size_t npts) { return npts <= (size_t)sweep_blocks(npts) * 64 * kDotsShort; }
+static bool sweep_short(const KrylovArgs& a) {
+  static_assert(((size_t)1 << 16) <= (size_t)kRedBlocks / 2 * 64 * kDotsShort, "a block's points in flight");
+  return a.nrhs == 1 && sweep_blocks(a.npts) < kRedBlocks;
+}
 
 // Where the sweep takes w = A u_j from: the stored vector (slot j+1), or, fused
 // with the right-preconditioned step, the stencil applied to z = Q u_j as each
@@ -2892,7 +2898,7 @@ hipError_t launch_arnoldi_dots(const KrylovArgs& a, int j, hipStream_t st) {
   };
   if (j > 8 * kDotsSlots) return hipErrorInvalidValue;
   if (j > 4 * kDotsSlots) go(k_arnoldi_dots<8, 0>, 8);
-  else if (sweep_short(a.npts)) go(k_arnoldi_dots<4, kDotsShort>, 4);
+  else if (sweep_short(a)) go(k_arnoldi_dots<4, kDotsShort>, 4);
   else go(k_arnoldi_dots<4, 0>, 4);
   hipLaunchKernelGGL(k_arnoldi_fin, dim3(a.nrhs), dim3(kFinThreads), 0, st, (const cpx<double>*)a.part, a.skip_step,
                      a.state, j, a.restart, a.host_stop, sweep_blocks(a.npts));
@@ -2921,7 +2927,7 @@ hipError_t launch_arnoldi_dots_stencil(const KrylovArgs& a, int j, const Stencil
   hipError_t e;
   if (j > 8 * kDotsSlots) return hipErrorInvalidValue;
   if (j > 4 * kDotsSlots) e = dots_st_dispatch<8, 0>(a, j, s, st);
-  else if (sweep_short(a.npts)) e = dots_st_dispatch<4, kDotsShort>(a, j, s, st);
+  else if (sweep_short(a)) e = dots_st_dispatch<4, kDotsShort>(a, j, s, st);
   else e = dots_st_dispatch<4, 0>(a, j, s, st);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_arnoldi_fin, dim3(a.nrhs), dim3(kFinThreads), 0, st, (const cpx<double>*)a.part, a.skip_step,

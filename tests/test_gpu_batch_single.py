@@ -53,6 +53,25 @@ def test_batch_solve_equals_single(hp, shape, m_real, kw):
     plan.close()
 
 
+# FP64, where one right-hand side on up to 2^16 points takes a sweep of its own
+@pytest.mark.parametrize("shape,side", [((64, 64), "right"), ((60, 54), "none"), ((128, 90), "left"), ((256, 256), "right"),
+                                        ((256, 250), "none"), ((256, 270), "right"), ((16, 16, 18), "right"),
+                                        ((40, 40, 40), "left"), ((48, 40, 36), "right")])
+def test_fp64_batch_solve_equals_single(hp, shape, side):
+    print(f"[case] FP64 batch solve {shape} {side}", flush=True)
+    omega = 2 * np.pi * min(shape) / 10
+    c = inputs.gaussian_random_field(shape, 4.0, sum(shape))
+    plan = hp.Plan(shape, omega, c, np.full(shape, 0.05 * omega), None, m_real=5, max_nrhs=2)
+    f = _sources(shape, 3)
+    opts = dict(rtol=1e-12, max_cycles=2, restart=21, side=side)   # sweeps over one and two rounds of vectors
+    x, info = plan.solve(f, **opts)
+    for k in range(3):
+        xk, ik = plan.solve(f[k].contiguous(), **opts)
+        assert ik[0].iters == info[k].iters
+        assert torch.equal(x[k], xk), float((x[k] - xk).abs().max() / xk.abs().max())
+    plan.close()
+
+
 def test_grouped_solves_equal_batch(hp):
     """Members with and without node splits, with either update, in one group."""
     print("[case] grouped against batch", flush=True)
