@@ -193,12 +193,14 @@ __device__ __forceinline__ void cols_body(
   // the workgroups of one XCD consecutive column tiles so that tiles sharing cache lines
   // meet in the same L2.  In the symbol pass tile counts that eight does not divide run on
   // over the node groups (in dispatch order: 1024 x 1000 FP64 108 us, now 78, mixed 70 and
-  // 56; 2048 x 2000 mixed 518 and 281, 2048 x 1944 FP64 1203 and 530).  The plain passes'
-  // wider tiles share no lines and keep it.
+  // 56; 2048 x 2000 mixed 518 and 281, 2048 x 1944 FP64 1203 and 530), where tiles are
+  // narrower than a cache line: wider ones share none to speak of and lose the spread over
+  // the XCDs (256 x 4800 mixed, three fields 59 us, 66 so; 128 x 1440 FP64 28.7 and 32.9).
+  // So do the plain passes' tiles.
   int tile = bx;
 #if HP_XCD_REMAP
   if ((gx & 7) == 0) tile = (bx & 7) * (gx >> 3) + (bx >> 3);
-  else if (MODE == 1) xcd_tile(bx, by, gx, gy, &tile, &by);
+  else if (MODE == 1 && C::TC * sizeof(cpx<TI>) < 128) xcd_tile(bx, by, gx, gy, &tile, &by);
 #endif
   // plain passes over node fields: slabs whose points never use this node are skipped
   if (MODE == 0 && slab_need != nullptr && slab_need[(size_t)fld * gy + by] == 0) return;
