@@ -62,7 +62,7 @@ __host__ __device__ constexpr int sweep_blocks(size_t npts) {
 
 // Mixed-radix lines held in LDS: those the register lines below do not take (lengths
 // without four radices of at most 16, FP64 column passes over powers of two above 2048,
-// FP32 Lagrange rows with radices above ten) and the schedules a tuning file asks for.  Stage radices in order, threads per line
+// the Lagrange rows that combine_line_plan leaves) and the schedules a tuning file asks for.  Stage radices in order, threads per line
 // and (column passes) lines per workgroup.  A thread holds at most E elements of a line: kGenRowE in pass A, gen_e<R>() in the
 // column passes and in pass C.
 constexpr int kGenRowE = 16;

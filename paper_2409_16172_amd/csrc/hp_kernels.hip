@@ -1334,20 +1334,24 @@ struct CombineL {
 };
 
 
-// Pass C's plan over mixed-radix rows.  Lagrange weights bound the kernel where its lines
-// fill the chip, and line splits then only repeat the records: up to four splits below 28k
-// threads, two below 72k, none above (applies with one / two / four splits: 200 x 320 FP64,
-// K = 19, one field (13k) 84 / 61 / 48 us, four (51k) 100 / 79 / 84; 576^2 FP32, K = 11, one
-// (41k) 84 / 65 / 90, two (83k) 95 / 100 / 135; 360 x 600 FP64, K = 7, sixteen (576k) 383 /
-// 442).  FP32 rows with radices above ten, which spill or run at two waves there, keep the
-// LDS lines in that mode (512 x 1296, K = 7, four fields: 119 us against 162; 1440^2 113
-// against 132, 1200 points equal).
+// Pass C's plan over mixed-radix rows.  Line splits pay while the lines of the plan's largest
+// launch leave the chip idle: up to four below 28k threads, two below 72k or, Lagrange apart,
+// where two lines of 65 to 96 threads take three wavefronts instead of four.  Applies with
+// one / two / four splits: 200 x 320 FP64 Lagrange, K = 19, one field (13k) 84 / 61 / 48 us,
+// four (51k) 100 / 79 / 84; 576^2 mixed, K = 11, two fields (83k, 72 threads a line) 70 / 62 /
+// 73; 512 x 1296 mixed, K = 7, four (295k) 147 / 200; 960 x 1152 FP64, K = 7, one (138k) 135 /
+// 146.  In FP32 Lagrange, rows with radices above ten (two waves per SIMD) or more than 256
+// threads (one workgroup a CU) keep the LDS lines: 512 x 1296, K = 7, four fields 119 us
+// against 162, 512 x 2000 77 against 99, 1440^2 113 against 132, 1200 points equal.  So do
+// FP64 ones of 257 to 384 threads, whose one workgroup leaves two waves of eight unused
+// (512 x 1944, K = 19, four fields 667 against 689; 400 threads 360 against 365).
 static bool combine_line_plan(const CombineArgs& a, LinePlan* lp) {
   if (!make_line_plan(a.real_kind, a.n, kLineComb, a.rows, a.K, a.tune.tc, lp)) return false;
-  if (interp_mode(a) != kInterpLagrange) return true;
-  if (a.real_kind == 1 && lp->rm > kLineRadixLo) return false;
+  const bool lag = interp_mode(a) == kInterpLagrange;
+  if (lag && (a.real_kind == 1 ? lp->rm > kLineRadixLo || lp->T > 256 : lp->T > 256 && lp->T <= 384)) return false;
   const long threads = (long)a.rows * a.batch * lp->T;
-  const int most = threads <= 28000 ? kLineSplits : threads <= 72000 ? 2 : 1;
+  const bool packs = !lag && lp->T > 64 && lp->T <= 96;
+  const int most = threads <= 28000 ? kLineSplits : threads <= 72000 || packs ? 2 : 1;
   return lp->splits <= most || make_line_plan(a.real_kind, a.n, kLineComb, a.rows, most, a.tune.tc, lp);
 }
 

@@ -728,7 +728,17 @@ hipError_t launch_line_cols(const LinePlan& p, const ColsArgs& a, hipStream_t st
 }
 
 template <typename R, typename TO, bool ACC, int IM>
-static hipError_t combine_go(const LinePlan& p, const CombineArgs& a, hipStream_t st) {
+static hipError_t combine_go(const LinePlan& plan, const CombineArgs& a, hipStream_t st) {
+  LinePlan p = plan;
+  if constexpr (IM == kInterpLagrange) {
+    // the weights' table beside the lines may cost a workgroup that the plan's second
+    // exchange region did not (1620 points FP64: one on a CU instead of two)
+    auto held = [&] { return (size_t)160 * 1024 / (line_lds(p, sizeof(cpx<R>), true) + kLagTable * sizeof(double)); };
+    const size_t two = held();
+    p.two_buf = 0;
+    const size_t waves = (p.T * p.L + 63) / 64, regs = 4 * line_waves(sizeof(R) == 8, p.rm, kLineComb, IM) / waves;
+    if (std::min(held(), std::max<size_t>(1, regs)) <= two) p.two_buf = plan.two_buf;
+  }
   const size_t lds = line_lds(p, sizeof(cpx<R>), true);
   const int nrow = p.L / p.splits;
   auto go = [&](auto kern) {

@@ -23,7 +23,9 @@ def hp():
 @pytest.mark.parametrize("order", [2, 3])
 @pytest.mark.parametrize("shape,precision,nrhs", [((200, 320), "fp64", 1), ((200, 320), "fp64", 4), ((200, 320), "mixed", 8),
                                                   ((200, 320), "mixed", 2), ((36, 1296), "mixed", 2), ((36, 1296), "fp64", 2),
-                                                  ((360, 600), "fp64", 3), ((10, 12, 90), "mixed", 3)])
+                                                  ((360, 600), "fp64", 3), ((10, 12, 90), "mixed", 3),
+                                                  ((18, 1944), "fp64", 2), ((18, 2000), "mixed", 2),
+                                                  ((18, 1620), "fp64", 2), ((18, 2500), "fp64", 1)])
 def test_lagrange_lines_match_oracle(orc, hp, shape, precision, nrhs, order):
     print(f"[case] line splits {shape} {precision} x{nrhs} order {order}", flush=True)
     rng = np.random.default_rng(sum(shape) + nrhs)
@@ -40,4 +42,25 @@ def test_lagrange_lines_match_oracle(orc, hp, shape, precision, nrhs, order):
     ref = orc.Problem(shape, omega, c, a, None, **kw).apply(v[k])
     assert rel(u[k].cpu().numpy(), ref) < (1e-12 if precision == "fp64" else 1e-5)
     assert torch.equal(u[k], plan.apply(vd[k].contiguous()))
+    plan.close()
+
+
+# linear rows on both sides of the thread counts where splits go from four to two to one, and
+# rows of 72 and 90 threads, which keep two
+@pytest.mark.parametrize("shape,precision,nrhs", [((180, 240), "fp64", 2), ((180, 240), "fp64", 8), ((128, 1440), "mixed", 1),
+                                                  ((128, 1440), "mixed", 4), ((100, 576), "fp64", 12), ((60, 720), "mixed", 16)])
+def test_linear_lines_match_oracle(orc, hp, shape, precision, nrhs):
+    print(f"[case] linear line splits {shape} {precision} x{nrhs}", flush=True)
+    rng = np.random.default_rng(sum(shape) + nrhs)
+    omega = 2 * np.pi * min(shape) / 8
+    c = 0.8 + 0.5 * rng.random(shape)
+    a = np.full(shape, 0.05 * omega)
+    kw = dict(m_real=9, a_floor=0.05 * omega)
+    plan = hp.Plan(shape, omega, c, a, None, precision=precision, max_nrhs=nrhs, **kw)
+    dt = torch.complex128 if precision == "fp64" else torch.complex64
+    v = rng.standard_normal((2,) + shape) + 1j * rng.standard_normal((2,) + shape)
+    vd = torch.from_numpy(v).to("cuda").to(dt)
+    u = plan.apply(vd)
+    assert rel(u[1].cpu().numpy(), orc.Problem(shape, omega, c, a, None, **kw).apply(v[1])) < (1e-12 if precision == "fp64" else 1e-5)
+    assert torch.equal(u[1], plan.apply(vd[1].contiguous()))
     plan.close()
