@@ -80,6 +80,7 @@ struct hp_plan_s {
   DevBuf posa;     // per point: position among the damping nodes (Ma >= 2)
   // node usage counts for the byte model of the passes
   double rows_used = 0;    // sum over pass-C rows of the nodes the row uses
+  double row_fill = 1;     // their average over the most that one row uses
   double slabs_used = 0;   // sum over nodes of the axis-0 indices that use the node
   int smask_thr = 0;       // mixed-radix lengths: threads per line storemask was built for
   DevBuf t, fields;                  // apply workspace
@@ -580,10 +581,13 @@ hp_status hp_plan_create(hp_plan* out, const hp_grid* grid, double omega, const 
 
   const int G = hp::combine_group_rows(P->real_kind(), nl);
   std::vector<uint64_t> gm((rows + G - 1) / G, 0);
+  int row_most = 1;
   for (size_t r = 0; r < rows; ++r) {
     gm[r / G] |= rm[r];
     P->rows_used += (double)__builtin_popcountll(rm[r]);
+    row_most = std::max(row_most, (int)__builtin_popcountll(rm[r]));
   }
+  P->row_fill = P->rows_used / ((double)rows * row_most);
   const int n0 = P->n[0];
   const size_t rows_per_slab = rows / n0;
   std::vector<uint8_t> need((size_t)P->K * n0, 0);
@@ -779,18 +783,23 @@ struct ApplyWs {
 // Fields of a batch that passes B, M and C take at once.  Where a field fills the chip by
 // itself and its used node rows fit the 256 MiB Infinity Cache (and a batch's do not), they
 // run the batch in parts that reuse the same node-field memory, so that passes M and C find
-// in the cache what pass B wrote.  The results do not depend on it.  Powers of two, in 3-D
-// or in FP64 with columns of up to 1024 points; two, four or eight fields, whole / in parts:
-// 3-D 1.02-1.2 (128^3 mixed, K = 19, four fields 795 -> 677 us; Lagrange 64 x 64 x 512 0.98
-// at worst), FP64 1024^2 and rows of 2048 points 1.03-1.47.  Elsewhere a part's last
-// workgroups leave more of the chip idle than the cache saves: FP64 columns of 2048 points
-// 0.90-1.12, mixed 2-D 0.82-1.13, mixed-radix grids 0.81-1.15 (1200 x 960 FP64, K = 19,
-// eight fields 1512 -> 1856 us).
+// in the cache what pass B wrote.  The results do not depend on it.  3-D grids (two, four or
+// eight fields, whole / in parts: powers of two 1.02-1.2, 128^3 mixed, K = 19, four fields
+// 795 -> 677 us; the others 0.97-1.15 for two and four); 2-D FP64 powers of two with columns
+// of up to 1024 points (1.03-1.47), and in mixed precision those of 2^21 points and more
+// (1024 x 2048 1.05-1.14) and grids without a power of two and columns of up to 1200 points
+// (1.0-1.09).  Elsewhere a part's last workgroups leave more of the chip idle than the cache
+// saves: FP64 columns of 2048 points 0.90-1.12, mixed 2-D powers of two 0.88-1.07, mixed-radix
+// columns or rows 0.81-1.01 (1200 x 960 FP64, K = 19, eight fields 1512 -> 1856 us).
 int batch_part(const hp_plan_s* P, int nrhs) {
   constexpr double kCache = 256.0 * (1 << 20);
-  for (int d = 0; d < P->dim; ++d)
-    if (!hp::is_pow2_len(P->n[d])) return nrhs;
-  if (P->dim == 2 && (P->prec != HP_FP64 || P->n[0] > 1024)) return nrhs;
+  if (P->dim == 2) {
+    const bool p0 = hp::is_pow2_len(P->n[0]), p1 = hp::is_pow2_len(P->n[1]);
+    const bool fits = P->prec == HP_FP64 ? p0 && p1 && P->n[0] <= 1024
+                      : p0 && p1         ? P->n[0] <= 1024 && P->npts >= ((size_t)1 << 21)
+                                         : !p0 && !p1 && P->n[0] <= 1200;
+    if (!fits) return nrhs;
+  }
   const double one = P->slabs_used * (double)(P->npts / P->n[0]) * (double)P->fsize();
   if (P->npts < ((size_t)1 << 20) || one > kCache || one * nrhs <= kCache) return nrhs;
   return std::max(1, (int)(kCache / one));
@@ -799,7 +808,8 @@ int batch_part(const hp_plan_s* P, int nrhs) {
 // Node splits of the plan's pass C under the choice t.
 int pass_c_splits(const hp_plan_s* P, const hp::PassTune& t) {
   const int nl = P->n[P->dim - 1];
-  return hp::combine_splits(P->real_kind(), nl, (int)(P->npts / nl), batch_part(P, P->max_nrhs), P->K, P->interp(), t);
+  return hp::combine_splits(P->real_kind(), nl, (int)(P->npts / nl), batch_part(P, P->max_nrhs), P->row_fill, P->K,
+                            P->interp(), t);
 }
 
 // Passes A and A' of an apply over nrhs fields: their spectra along the last axes, into wt.
@@ -871,7 +881,7 @@ hipError_t apply_back(hp_plan_s* P, void* u, int out_kind, size_t out_rs, bool a
   c.real_kind = rk; c.out_kind = out_kind; c.accumulate = acc ? 1 : 0; c.n = nl;
   c.fields = wf; c.fs = np; c.frs = np * P->K; c.pos = (const double*)P->pos.p;
   c.grpmask = (const uint64_t*)P->grpmask.p; c.rowmask = (const uint64_t*)P->rowmask.p; c.out = u; c.out_rs = out_rs; c.rows = rows; c.K = P->K;
-  c.M = P->M; c.Mt = P->Mt; c.mo = P->mo; c.nrhs = nrhs; c.batch = batch_part(P, P->max_nrhs); c.tw = P->tw(P->dim - 1); c.stw = P->stw(P->dim - 1); c.skip = skip;
+  c.M = P->M; c.Mt = P->Mt; c.mo = P->mo; c.nrhs = nrhs; c.batch = batch_part(P, P->max_nrhs); c.row_fill = P->row_fill; c.tw = P->tw(P->dim - 1); c.stw = P->stw(P->dim - 1); c.skip = skip;
   c.order = P->order; c.lag = (const double*)P->lagtab.p;
   c.posa = (const double*)P->posa.p; c.Ma = P->Ma;
   c.tune = P->tune[4];

@@ -222,6 +222,7 @@ struct CombineArgs {
   size_t out_rs;
   int rows, K, M, Mt, mo, nrhs;
   int batch;           // right-hand sides of the plan's largest launch (nrhs: of this one)
+  double row_fill;     // nodes that a row uses on the average, over the most that one uses
   const void* tw;
   const void* stw;     // register lines: the stage table of line_stage_table
   const int* skip;
@@ -238,8 +239,9 @@ hipError_t launch_combine(const CombineArgs& a, hipStream_t st);
 hipError_t launch_line_combine(const LinePlan& p, const CombineArgs& a, hipStream_t st);
 int combine_group_rows(int real_kind, int n);        // rows per workgroup of pass C
 // Node splits of pass C over `rows` power-of-two lines and at most `batch` right-hand sides a
-// launch, K nodes, interpolation mode `interp` (1 for lines that cannot split).
-int combine_splits(int real_kind, int n, int rows, int batch, int K, int interp, const PassTune& tune);
+// launch, K nodes, interpolation mode `interp` (1 for lines that cannot split); row_fill as
+// in CombineArgs.
+int combine_splits(int real_kind, int n, int rows, int batch, double row_fill, int K, int interp, const PassTune& tune);
 int symbol_pass_line_threads(int real_kind, int n);  // threads per line T of pass B
 // threads per line of the built-in mixed-radix symbol-pass plan (0 if n has none) and
 // the elements each thread holds

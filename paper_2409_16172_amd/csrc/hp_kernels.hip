@@ -195,12 +195,15 @@ __device__ __forceinline__ void cols_body(
   // over the node groups (in dispatch order: 1024 x 1000 FP64 108 us, now 78, mixed 70 and
   // 56; 2048 x 2000 mixed 518 and 281, 2048 x 1944 FP64 1203 and 530), where tiles are
   // narrower than a cache line: wider ones share none to speak of and lose the spread over
-  // the XCDs (256 x 4800 mixed, three fields 59 us, 66 so; 128 x 1440 FP64 28.7 and 32.9).
+  // the XCDs (256 x 4800 mixed, three fields 59 us, 66 so), but take it where the node fields
+  // fit the eight 4 MiB L2s, in which passes M and C then find them (128 x 48 x 40 mixed, K =
+  // 11: apply 59 us in dispatch order, 55 so).
   // So do the plain passes' tiles.
   int tile = bx;
 #if HP_XCD_REMAP
   if ((gx & 7) == 0) tile = (bx & 7) * (gx >> 3) + (bx >> 3);
-  else if (MODE == 1 && C::TC * sizeof(cpx<TI>) < 128) xcd_tile(bx, by, gx, gy, &tile, &by);
+  else if (MODE == 1 && (C::TC * sizeof(cpx<TI>) < 128 || (size_t)N * S * K * sizeof(cpx<R>) <= ((size_t)32 << 20)))
+    xcd_tile(bx, by, gx, gy, &tile, &by);
 #endif
   // plain passes over node fields: slabs whose points never use this node are skipped
   if (MODE == 0 && slab_need != nullptr && slab_need[(size_t)fld * gy + by] == 0) return;
@@ -399,12 +402,8 @@ __device__ __forceinline__ void rows_combine_body(
   }
 }
 
-// Waves per SIMD the kernel is compiled for: two, or under Lagrange interpolation, whose
-// records and weights keep up to 34 registers more than two leave (FP32 4096), as many as
-// fit without spills.
-constexpr int combine_waves(int im) { return im == kInterpLagrange ? 1 : 2; }
 template <typename R, typename TO, int N, bool ACC, int IM, int NS = 1>
-__global__ __launch_bounds__((CombCfg<R, N>::THREADS * NS)) __attribute__((amdgpu_waves_per_eu(combine_waves(IM)))) void k_rows_combine(
+__global__ __launch_bounds__((CombCfg<R, N>::THREADS * NS)) __attribute__((amdgpu_waves_per_eu(2))) void k_rows_combine(
     const cpx<R>* __restrict__ fields, size_t fs, size_t frs, const double* __restrict__ pos,
     const uint64_t* __restrict__ grpmask, const uint64_t* __restrict__ rowmask, cpx<TO>* __restrict__ out,
     size_t out_rs, int rows, int K, int M, int Mt, int mo, const cpx<R>* __restrict__ tw,
@@ -1029,13 +1028,16 @@ static bool make_col_plan(int n, int S, int mode, GenPlan* gp, const PassTune& t
 static bool combine_splits_ok(int real_kind, int n) { return is_pow2_len(n) && n <= (real_kind == 0 ? 64 * HP_E64 : 64 * HP_E32); }
 
 // Node splits, or as tuned (the tuner's node-group field).  The choice depends on the plan
-// only (for its largest launch), so that a batch sums in the order a
-// single field does, and a step in a grouped launch in the order of the member's own step.
-// `fill` wavefronts hold a node's rows without splits; four times as many fill the 1024
-// SIMDs from 512 on, and then the records decoded four times, the nodes of a group's other
-// rows and the two barriers tell.  Measured as applies without splits / with four, rows of
-// 64 to 1024 points, 128 to 1024 of them, one to eight right-hand sides (eight splits gave
-// nothing over four):
+// only (for its largest launch), so that a batch sums in the order a single field does, and
+// a step in a grouped launch in the order of the member's own step.
+// `fill` of the wavefronts that hold a node's rows without splits are busy to the end (the
+// rows of a medium use different numbers of nodes, row_fill on the average of the most,
+// which tells from eight nodes on: 512^2 FP64 with a small inclusion, K = 24, three fields,
+// pass C 32 us without splits, 17 with; 768 x 512 mixed, K = 4, 11 and 14);
+// four times as many fill the 1024 SIMDs from 512 on, and then the records decoded four
+// times, the nodes of a group's other rows and the two barriers tell.  Measured as applies
+// without splits / with four, rows of 64 to 1024 points, 128 to 1024 of them, one to eight
+// right-hand sides (eight splits gave nothing over four):
 //   up to 512: linear 1.03-1.15 at 512 and 1.2-1.7 at 128 (K = 5 to 19; 0.97-1.0 at K = 2),
 //     Lagrange 1.0-1.5 at 512, bilinear 1.02-2.0.  FP32 rows of 256 points, four to a
 //     wavefront there but one to a wavefront without, in the other modes: 0.85-0.99 below
@@ -1045,18 +1047,24 @@ static bool combine_splits_ok(int real_kind, int n) { return is_pow2_len(n) && n
 //     wavefront group (FP32 128, FP64 256 points and below), 0.7-1.0 elsewhere;
 //   above: FP32 linear rows of 256 points 1.18-1.29 at 2048 (four wavefronts on one row's
 //     nodes read longer runs at once than one on each of four rows: 256^3, K = 19, pass C
-//     463 -> 334 us) and of 512 from eleven nodes on 1.01-1.14; all others 0.5-1.04.
-int combine_splits(int real_kind, int n, int rows, int batch, int K, int interp, const PassTune& tune) {
+//     463 -> 334 us) and of 512 from eleven nodes on 1.01-1.14; FP32 linear of sixteen nodes
+//     and more up to 2048 (1024 points 3072) 1.0-1.12; FP64 linear with at most 256 row
+//     groups a field, or 1024 and eight nodes, 0.94-1.07 on powers of two and 1.05-1.12 on
+//     columns of mixed radix (240 x 512, K = 7, eight fields 73 -> 65 us); others 0.5-1.04.
+int combine_splits(int real_kind, int n, int rows, int batch, double row_fill, int K, int interp, const PassTune& tune) {
   if (!combine_splits_ok(real_kind, n)) return 1;
   if (tune.ng > 0) return tune.ng == kCombineSplits ? kCombineSplits : 1;
-  const int g = combine_group_rows(real_kind, n);
-  const long fill = (long)((rows + g - 1) / g) * batch;
+  const int g = combine_group_rows(real_kind, n), groups = (rows + g - 1) / g;
+  const double fill = (double)groups * batch * (K < 8 ? 1.0 : row_fill);
   const bool fp32 = real_kind == 1, many = K >= 11;
   if (K < 3) return 1;
   bool split;
   if (fp32 && n == 256 && interp != kInterpLinear) split = many && fill <= 512;
   else if (fill <= 512) split = true;
-  else if (interp == kInterpLinear) split = (fp32 && n == 256) || (many && (fill <= 1024 || (fp32 && n == 512)));
+  else if (interp == kInterpLinear)
+    split = (fp32 && n == 256) || (many && (fill <= 1024 || (fp32 && n == 512))) ||
+            (fp32 ? K >= 16 && groups <= 1024 && fill <= (n == 1024 ? 3072 : 2048)
+                  : (K >= 3 && groups <= 256) || (K >= 8 && groups <= 1024));
   else if (interp == kInterpLagrange) split = fill <= 1024 && n <= (fp32 ? 128 : 256);
   else split = fp32 && many && fill <= 1024;
   return split ? kCombineSplits : 1;
@@ -1302,7 +1310,7 @@ struct CombineL {
       using C = CombCfg<R, N>;
       dim3 grid((a.rows + C::G - 1) / C::G, a.nrhs);
       if constexpr (combine_splits_fit<R, N>()) {
-        if (combine_splits(sizeof(R) == 8 ? 0 : 1, N, a.rows, a.batch, a.K, interp_mode(a), a.tune) == kCombineSplits) {
+        if (combine_splits(sizeof(R) == 8 ? 0 : 1, N, a.rows, a.batch, a.row_fill, a.K, interp_mode(a), a.tune) == kCombineSplits) {
           combine_launch<R, TO, N, ACC, kCombineSplits>(a, grid, st);
           return hipGetLastError();
         }
@@ -1334,24 +1342,28 @@ struct CombineL {
 };
 
 
-// Pass C's plan over mixed-radix rows.  Line splits pay while the lines of the plan's largest
-// launch leave the chip idle: up to four below 28k threads, two below 72k or, Lagrange apart,
-// where two lines of 65 to 96 threads take three wavefronts instead of four.  Applies with
-// one / two / four splits: 200 x 320 FP64 Lagrange, K = 19, one field (13k) 84 / 61 / 48 us,
-// four (51k) 100 / 79 / 84; 576^2 mixed, K = 11, two fields (83k, 72 threads a line) 70 / 62 /
-// 73; 512 x 1296 mixed, K = 7, four (295k) 147 / 200; 960 x 1152 FP64, K = 7, one (138k) 135 /
-// 146.  In FP32 Lagrange, rows with radices above ten (two waves per SIMD) or more than 256
-// threads (one workgroup a CU) keep the LDS lines: 512 x 1296, K = 7, four fields 119 us
-// against 162, 512 x 2000 77 against 99, 1440^2 113 against 132, 1200 points equal.  So do
-// FP64 ones of 257 to 384 threads, whose one workgroup leaves two waves of eight unused
-// (512 x 1944, K = 19, four fields 667 against 689; 400 threads 360 against 365).
+// Pass C's plan over mixed-radix rows.  The plan's line splits (make_line_plan) suit rows
+// that leave the chip idle; fewer where that is measured better:
+//   linear rows with radices above ten, whose lines of 108 threads and more fill the chip from
+//   72k threads on (row_fill as in combine_splits): none.  512 x 1296 mixed, K = 7, four
+//   fields (295k) 147 us, 200 with two; 960 x 1152 FP64, K = 7, one (138k) 135 and 146;
+//   Lagrange lines of 65 to 96 threads from 28k on: two, not four (576^2 mixed, K = 11, one
+//   field (41k) 65 us and 90, four 149 and 230; below, 256 x 648 with a small inclusion, K =
+//   16 (3k), 60 and 47).
+// Lagrange rows keep the LDS lines in FP32 with three radices some above ten, or more than
+// 256 threads (one workgroup a CU): 512 x 1296, K = 7, four fields 119 us against 162, 512 x
+// 2000 77 against 99, 1440^2 113 against 132, 1200 points equal; in FP64 with 257 to 384
+// threads, whose one workgroup leaves two waves of eight unused (512 x 1944, K = 19, four
+// fields 667 against 689; 400 threads 360 against 365).
 static bool combine_line_plan(const CombineArgs& a, LinePlan* lp) {
   if (!make_line_plan(a.real_kind, a.n, kLineComb, a.rows, a.K, a.tune.tc, lp)) return false;
-  const bool lag = interp_mode(a) == kInterpLagrange;
-  if (lag && (a.real_kind == 1 ? lp->rm > kLineRadixLo || lp->T > 256 : lp->T > 256 && lp->T <= 384)) return false;
-  const long threads = (long)a.rows * a.batch * lp->T;
-  const bool packs = !lag && lp->T > 64 && lp->T <= 96;
-  const int most = threads <= 28000 ? kLineSplits : threads <= 72000 || packs ? 2 : 1;
+  const int im = interp_mode(a);
+  const bool fp32 = a.real_kind == 1, wide = lp->rm > kLineRadixLo;
+  if (im == kInterpLagrange && (fp32 ? (wide && lp->nst > 2) || lp->T > 256 : lp->T > 256 && lp->T <= 384)) return false;
+  const double threads = (double)a.rows * a.batch * lp->T * a.row_fill;
+  int most = kLineSplits;
+  if (im == kInterpLinear && wide && lp->T > 96 && threads > 72000) most = 1;
+  else if (im == kInterpLagrange && lp->T > 64 && lp->T <= 96 && threads > 28000) most = 2;
   return lp->splits <= most || make_line_plan(a.real_kind, a.n, kLineComb, a.rows, most, a.tune.tc, lp);
 }
 

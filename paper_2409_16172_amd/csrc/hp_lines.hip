@@ -36,13 +36,13 @@ __device__ __forceinline__ void line_barrier() {
 // with radices up to kLineRadixLo, two above.  FP32: four and, in pass C with radices up
 // to 16, three (pass B takes its 29 spilled registers for the fourth wave: 1920 x 1500,
 // K = 19, 268 -> 233 us; pass C does not: 2400^2, K = 8, 52 us with three, 71 with four).
-// Pass C in the other interpolation modes, whose records and weights take more registers,
-// gives a wave up where it would spill 28 to 288 bytes a lane (Lagrange 576^2 FP64, K = 15,
-// sixteen fields: 1450 -> 900 us; 512 x 1296 FP32, three fields: 269 -> 206).
+// FP64 pass C in the other interpolation modes, whose records and weights take more
+// registers, gives a wave up where it would spill 172 to 288 bytes a lane (Lagrange 576^2,
+// K = 15, sixteen fields: 1450 -> 900 us; FP32 spills 32 to 148 and is better off so: 320 x
+// 486, K = 8, 14 us, 18 with a wave less).
 __host__ __device__ constexpr int line_waves(bool fp64, int rm, int kind, int im = kInterpLinear) {
-  const bool less = kind == kLineComb && (im == kInterpLagrange || (im == kInterpBilinear && fp64));
-  return fp64 ? (rm <= kLineRadixLo && !less ? 3 : 2)
-              : (rm <= kLineRadixLo || kind == kLineSym ? 4 : 3) - (less ? 1 : 0);
+  const bool less = kind == kLineComb && im != kInterpLinear;
+  return fp64 ? (rm <= kLineRadixLo && !less ? 3 : 2) : (rm <= kLineRadixLo || kind == kLineSym ? 4 : 3);
 }
 #define HP_LINE_WAVES(R, RM, ...) __attribute__((amdgpu_waves_per_eu(line_waves(sizeof(R) == 8, RM, __VA_ARGS__))))
 

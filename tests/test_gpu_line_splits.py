@@ -1,6 +1,6 @@
-"""Pass C of mixed-radix rows under Lagrange interpolation on both sides of its choices: four,
-two or no line splits by the threads of the plan's largest launch, and FP32 rows whose radices
-exceed ten (LDS lines), against the oracle; one field equals the same field of a batch."""
+"""Pass C of mixed-radix rows on both sides of its choices: line splits by the radices and the
+threads of the plan's largest launch, and the Lagrange rows that keep the LDS lines, against
+the oracle; one field equals the same field of a batch."""
 import numpy as np
 import pytest
 import torch
@@ -24,6 +24,7 @@ def hp():
 @pytest.mark.parametrize("shape,precision,nrhs", [((200, 320), "fp64", 1), ((200, 320), "fp64", 4), ((200, 320), "mixed", 8),
                                                   ((200, 320), "mixed", 2), ((36, 1296), "mixed", 2), ((36, 1296), "fp64", 2),
                                                   ((360, 600), "fp64", 3), ((10, 12, 90), "mixed", 3),
+                                                  ((300, 576), "mixed", 1), ((400, 576), "mixed", 2), ((60, 144), "mixed", 2),
                                                   ((18, 1944), "fp64", 2), ((18, 2000), "mixed", 2),
                                                   ((18, 1620), "fp64", 2), ((18, 2500), "fp64", 1)])
 def test_lagrange_lines_match_oracle(orc, hp, shape, precision, nrhs, order):
@@ -45,8 +46,8 @@ def test_lagrange_lines_match_oracle(orc, hp, shape, precision, nrhs, order):
     plan.close()
 
 
-# linear rows on both sides of the thread counts where splits go from four to two to one, and
-# rows of 72 and 90 threads, which keep two
+# linear rows with radices above ten (1440) on both sides of 72k threads, others with four and
+# two splits
 @pytest.mark.parametrize("shape,precision,nrhs", [((180, 240), "fp64", 2), ((180, 240), "fp64", 8), ((128, 1440), "mixed", 1),
                                                   ((128, 1440), "mixed", 4), ((100, 576), "fp64", 12), ((60, 720), "mixed", 16)])
 def test_linear_lines_match_oracle(orc, hp, shape, precision, nrhs):
